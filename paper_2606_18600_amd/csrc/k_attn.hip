@@ -19,8 +19,8 @@
 //   cache), with the causal mask applied per row. Both products on
 //   v_mfma_f32_32x32x16_bf16, with operands gathered per lane from the same
 //   fragments (staged in LDS).
-// * attn_f32_kernel: plain fp32 SIMT attention, one wave per (token, head),
-//   for the fp32 mode.
+// * attn_f32_kernel: the fp32 mode, prefill and decode rows alike: one
+//   workgroup per (up to 16 (token, head) rows, kv head) on fp32 MFMA.
 #include <type_traits>
 
 #include "common.hpp"
@@ -576,66 +576,206 @@ void attn_prefill_bf16(
     }
 }
 
-// fp32 mode: one wave per (token, query head), keys [0, pos] of its sequence.
-// (D is a template argument so that the score and value loops unroll and
-// issue their loads ahead of the dependent FMA chains.)
+// fp32 mode, prefill and decode rows alike: one workgroup of kF32Waves waves
+// per (P consecutive tokens, kv head, run); its rows (at most 16) are the tokens'
+// (token, head) pairs. A run is the tokens of one sequence among the P; each
+// run has a block of its own (blockIdx.z; the blocks past the last run leave
+// at once), so that neither its chain of keys nor its values mix with another
+// request's. Wave w takes every kF32Waves-th 16-key block, in fp32
+// throughout, on v_mfma_f32_16x16x4_f32:
+//   S^T[key][row]: A = K, lane l: key l % 16, B = Q^T, lane l: row l % 16,
+//     step (j, e): d 32 j + 8 (l / 16) + e, the 8 consecutive floats the lane
+//     holds of K fragment j. C, lane l, value r: row l % 16, key 4 (l / 16) + r.
+//   O^T[d][row] += V^T P^T, step r: B = value r of the S^T tile as it stands,
+//     A = V^T, lane l: d 16 t + l % 16, the same key: of the lane's 8 floats
+//     of V fragment t / 2, number 4 (t % 2) + r.
+// The waves' (max, sum, output) are combined through LDS at the end. The fp32
+// mode's batches are small, so what bounds it is the chain of one row's keys:
+// eight waves share it, and a key that is read serves up to 16 rows. 454 rows
+// of 8 heads, up to 900 keys each: 117 us with one wave per (token, head), 45
+// with the runs of a block one after another, 26 with a block per run.
+constexpr int kF32Waves = 8;
+
 template <int D>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q,
-                                                       const float* __restrict__ kv, int n_kv,
-                                                       SegTables tabs,
-                                                       const int32_t* __restrict__ tok_seq,
-                                                       const int32_t* __restrict__ tok_pos,
-                                                       int t_begin, int n_q,
-                                                       float* __restrict__ out) {
-  const int t = t_begin + blockIdx.x;
-  const int h = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (h >= n_q) return;
-  const int lane = threadIdx.x & 63;
-  const int kvh = h / (n_q / n_kv);
-  const int pos = tok_pos[t];
-  const int32_t* bt = seq_table(tabs, tok_seq[t]);
-  const float* qp = q + ((size_t)t * n_q + h) * D;
-  const float scale = 1.0f / sqrtf((float)D);
-  const size_t plane = (size_t)kBlock * D;
-  float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
-  for (int c0 = 0; c0 <= pos; c0 += 64) {
-    const int key = c0 + lane;
-    float s = -INFINITY;
-    if (key <= pos) {
-      const float* kp = kv + ((size_t)bt[key / kBlock] * n_kv + kvh) * 2 * plane;
-      float acc = 0.f;
-#pragma unroll
-      for (int e = 0; e < D; ++e) acc = fmaf(qp[e], kp[kv_k_offset(key % kBlock, e)], acc);
-      s = acc * scale;
+__global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ kv, int n_kv, SegTables tabs,
+    const int32_t* __restrict__ tok_seq, const int32_t* __restrict__ tok_pos, int t_begin,
+    int t_end, int P, int n_q, float* __restrict__ out) {
+  constexpr int NW = kF32Waves, NJ = D / 32, NT = D / 16;
+  __shared__ float s_ml[NW][2][16];
+  __shared__ float s_o[NW / 2][16][D + 4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kvh = blockIdx.y;
+  int t0 = t_begin + blockIdx.x * P, np = min(P, t_end - t0);
+  for (int z = 0;; ++z) {  // tokens [t0, t0 + np): this block's run
+    int r1 = 1;
+    while (r1 < np && tok_seq[t0 + r1] == tok_seq[t0]) ++r1;
+    if (z == (int)blockIdx.z) {
+      np = r1;
+      break;
     }
-    const float cm = wave_max(s);
-    const float mn = fmaxf(m, cm);
-    const float alpha = expf(m - mn);
-    const float p = key <= pos ? expf(s - mn) : 0.f;
-    l = l * alpha + wave_sum(p);
-    o0 *= alpha;
-    o1 *= alpha;
-    auto pv = [&](int j) {
-      const float pj = __shfl(p, j, 64);
-      const int kj = c0 + j;
-      const float* vp = kv + ((size_t)bt[kj / kBlock] * n_kv + kvh) * 2 * plane + plane;
-      o0 = fmaf(pj, vp[kv_v_offset(kj % kBlock, lane)], o0);
-      if (D > 64) o1 = fmaf(pj, vp[kv_v_offset(kj % kBlock, lane + 64)], o1);
-    };
-    // whole 64-key chunks unrolled (a loop with a shuffle and a run-time
-    // trip count is not), the last partial chunk key by key
-    const int nk = min(64, pos + 1 - c0);
-    if (nk == 64) {
-#pragma unroll 8
-      for (int j = 0; j < 64; ++j) pv(j);
-    } else {
-      for (int j = 0; j < nk; ++j) pv(j);
-    }
-    m = mn;
+    if (r1 == np) return;  // fewer runs than blocks
+    t0 += r1;
+    np -= r1;
   }
-  float* op = out + ((size_t)t * n_q + h) * D;
-  op[lane] = o0 / l;
-  if (D > 64) op[lane + 64] = o1 / l;
+  const int G = n_q / n_kv;
+  const float scale = 1.0f / sqrtf((float)D);
+  const int row = lane & 15, quad = lane >> 4;
+  const int rt = row / G;               // this row's token of the run
+  const int tc = t0 + min(rt, np - 1);  // (rows past the run are masked, and not stored)
+  const int rpos = rt < np ? tok_pos[tc] : -1;
+  f32x4_t qf[NJ][2];
+  {
+    const float* qp = q + ((size_t)tc * n_q + kvh * G + row % G) * D + quad * 8;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      qf[j][0] = *(const f32x4_t*)(qp + j * 32);
+      qf[j][1] = *(const f32x4_t*)(qp + j * 32 + 4);
+    }
+  }
+  const size_t plane = (size_t)kBlock * D;
+  float m = -INFINITY, l = 0.f;
+  f32x4_t o[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) o[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  const int32_t* bt = seq_table(tabs, tok_seq[t0]);
+  // positions grow along a run, so its last token sees the most keys
+  const int first = tok_pos[t0], last = tok_pos[t0 + np - 1];
+  const int nb = last / kBlock + 1;
+  // K is loaded a block ahead, V at the start of its block
+  f32x4_t kf[NJ][2], vf[NJ][2], kn[NJ][2];
+  const float *vp = nullptr, *vn = nullptr;
+  int ids = 0, w0 = 0;  // lane i: id of this wave's block number w0 + i
+  auto load = [&](int b) {
+    const int i = (b - wave) / NW;
+    if (i - w0 >= 64 || i == 0) {
+      w0 = i;
+      ids = bt[min(b + lane * NW, nb - 1)];
+    }
+    const int id = __builtin_amdgcn_readlane(ids, i - w0);
+    const float* kp = kv + ((size_t)id * n_kv + kvh) * 2 * plane + lane * 8;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      kn[j][0] = *(const f32x4_t*)(kp + j * 512);
+      kn[j][1] = *(const f32x4_t*)(kp + j * 512 + 4);
+    }
+    vn = kp + plane;
+  };
+  if (wave < nb) load(wave);
+  for (int b = wave; b < nb; b += NW) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      kf[j][0] = kn[j][0];
+      kf[j][1] = kn[j][1];
+    }
+    vp = vn;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      vf[j][0] = *(const f32x4_t*)(vp + j * 512);
+      vf[j][1] = *(const f32x4_t*)(vp + j * 512 + 4);
+    }
+    if (b + NW < nb) load(b + NW);
+    // two chains of products, so that one's latency hides behind the other
+    f32x4_t s0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        s0 = mfma16x16x4(kf[j][0][e], qf[j][0][e], s0);
+        s1 = mfma16x16x4(kf[j][1][e], qf[j][1][e], s1);
+      }
+    float sc[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      sc[r] = b * kBlock + quad * 4 + r <= rpos ? (s0[r] + s1[r]) * scale : -INFINITY;
+    const float bm = row4_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+    const float mn = fmaxf(m, bm);
+    // a row whose keys are all masked so far keeps weight 0 everywhere
+    const float ref = mn == -INFINITY ? 0.f : mn;
+    const float alpha = expf(m - ref);
+    float p[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p[r] = expf(sc[r] - ref);
+    l = l * alpha + row4_sum((p[0] + p[1]) + (p[2] + p[3]));
+    m = mn;
+    auto pv = [&](bool take) {  // other rows keep their output
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        f32x4_t n = o[t] * alpha;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) n = mfma16x16x4(vf[t / 2][t % 2][r], p[r], n);
+        o[t] = take ? n : o[t];
+      }
+    };
+    // drop the values of keys past `end` (slots not written yet, or later
+    // tokens of the run)
+    auto drop_past = [&](int end) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool in = b * kBlock + quad * 4 + r <= end;
+          vf[j][0][r] = in ? vf[j][0][r] : 0.f;
+          vf[j][1][r] = in ? vf[j][1][r] : 0.f;
+        }
+    };
+    if (b * kBlock + kBlock - 1 <= first) {
+      pv(true);
+      continue;
+    }
+    // A block that some rows of the run see only in part: a weight of zero
+    // does not keep a later token's infinities and NaN out of a product.
+    drop_past(last);
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        bad |= !(fabsf(vf[j][0][r]) < INFINITY) || !(fabsf(vf[j][1][r]) < INFINITY);
+    if (np == 1 || __builtin_amdgcn_ballot_w64(bad) == 0) {
+      pv(true);
+      continue;
+    }
+    for (int i = np - 1; i >= 0; --i) {  // token by token, from the last
+      drop_past(tok_pos[t0 + i]);
+      pv(rt == i);
+    }
+  }
+
+  if (quad == 0) {
+    s_ml[wave][0][row] = m;
+    s_ml[wave][1][row] = l;
+  }
+  __syncthreads();
+  float M = -INFINITY, L = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) M = fmaxf(M, s_ml[w][0][row]);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) L += expf(s_ml[w][0][row] - M) * s_ml[w][1][row];
+  const float f = expf(m - M) / L;  // a token's row sees key 0, so M is finite there
+  // the upper half of the waves, then the lower half on top of it
+  if (wave >= NW / 2) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) *(f32x4_t*)&s_o[wave - NW / 2][row][t * 16 + quad * 4] = o[t] * f;
+  }
+  __syncthreads();
+  if (wave < NW / 2) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      f32x4_t* e = (f32x4_t*)&s_o[wave][row][t * 16 + quad * 4];
+      *e = *e + o[t] * f;
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 16 * D; i += NW * 64) {
+    const int r = i / D, d = i % D;
+    if (r / G >= np) continue;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW / 2; ++w) v += s_o[w][r][d];
+    out[((size_t)(t0 + r / G) * n_q + kvh * G + r % G) * D + d] = v;
+  }
 }
 
 }  // namespace
@@ -714,14 +854,21 @@ hipError_t attn_f32(const float* q, KVLayer kv, SegTables tabs, const int32_t* t
                     const int32_t* tok_pos, int t_begin, int n_tok, int n_q, float* out,
                     hipStream_t s) {
   if (n_tok == 0) return hipSuccess;
-  if (kv.head_dim != 64 && kv.head_dim != 128) return hipErrorInvalidValue;
-  dim3 grid(n_tok, (n_q + 3) / 4);
+  // whole 16-row tiles, unless that leaves more than half of the CUs without
+  // a block: then fewer tokens (and more padding rows) per block
+  int P = 16 / (n_q / kv.n_kv);
+  while (P > 1 && (long)((n_tok + P - 1) / P) * kv.n_kv < 128) P /= 2;
+  dim3 grid((n_tok + P - 1) / P, kv.n_kv, P);
   if (kv.head_dim == 128)
-    attn_f32_kernel<128><<<grid, 256, 0, s>>>(q, (const float*)kv.base, kv.n_kv, tabs, tok_seq,
-                                              tok_pos, t_begin, n_q, out);
+    attn_f32_kernel<128><<<grid, kF32Waves * 64, 0, s>>>(q, (const float*)kv.base, kv.n_kv, tabs,
+                                                         tok_seq, tok_pos, t_begin,
+                                                         t_begin + n_tok, P, n_q, out);
+  else if (kv.head_dim == 64)
+    attn_f32_kernel<64><<<grid, kF32Waves * 64, 0, s>>>(q, (const float*)kv.base, kv.n_kv, tabs,
+                                                        tok_seq, tok_pos, t_begin,
+                                                        t_begin + n_tok, P, n_q, out);
   else
-    attn_f32_kernel<64><<<grid, 256, 0, s>>>(q, (const float*)kv.base, kv.n_kv, tabs, tok_seq,
-                                             tok_pos, t_begin, n_q, out);
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

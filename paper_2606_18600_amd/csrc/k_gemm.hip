@@ -19,9 +19,8 @@
 //   weight fragments copied HBM -> LDS with direct loads (64-wide k steps,
 //   double-buffered), A fragments loaded straight into registers one or two
 //   stages ahead; epilogues: fp32 store, residual add, SwiGLU, query RoPE.
-// * gemm_tiled_f32: plain fp32 SIMT tiles (32 or 64 wide) for the fp32 mode
-//   (row-major); gemv_f32: fp32 products of at most 8 rows, one wave per
-//   output column.
+// * gemm_f32: fp32 MFMA tiles for the fp32 mode (row-major); gemv_f32: fp32
+//   products of at most 8 rows, one wave per output column.
 #include <algorithm>
 #include <cstdlib>
 #include <type_traits>
@@ -824,79 +823,167 @@ __global__ __launch_bounds__(WM * WN * 64, 512 / (WM * WN * 64)) void gemm_tiled
 }
 
 // ---------------------------------------------------------------------------
-// fp32 SIMT tiled GEMM (fp32 mode, row-major operands)
+// fp32 GEMM (fp32 mode, row-major operands)
 // ---------------------------------------------------------------------------
-constexpr int TF_K = 16;
+// fp32 operands and accumulators on v_mfma_f32_32x32x2_f32 (every product and
+// sum in 32 bits). A wave owns RT x CT tiles of 32 x 32; WM x WN such waves
+// cover the block tile and KS groups of them take a K range each, added
+// through LDS in range order. Bound: the fp32 matrix rate is a sixteenth of
+// the bf16 one, so an operand byte feeds its product slowly enough to come
+// straight from L1/L2 (16 B per clock and CU at 2 x 2 tiles per wave); LDS
+// staging would add a barrier per step and save nothing. What the fp32 mode's
+// sizes (a few hundred rows) lack is blocks, hence small tiles and K ranges
+// within a block. A lane loads 4 consecutive k of its row at a time (lane l:
+// row l % 32, k 8 v + 4 (l / 32) .. + 3), and step (v, e) multiplies k 8 v + e
+// and 8 v + 4 + e, the same permutation of k for both operands. Rows and columns past the end repeat
+// the last one and are not stored. Measured against SIMT tiles of 64 or 32
+// columns with LDS staging: 454 x 1280 x 512 91 -> 16.5 us, 454 x 512 x 1024
+// 63 -> 14 us, 151 x 256 x 704 58 -> 11 us. (KC = 64 on the small tiles, all
+// of a wave's K in flight at once, was slower: 16.5 -> 22.8 us.)
+//
+// EPI_SWIGLU: N = 2 F, gate rows then up rows; CT = 2, tile 0 holds 32 gate
+// columns and tile 1 the matching up columns, and out is [M, F].
+// the caller's fp32 weights may lie at any multiple of 4 bytes
+typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
 
-// Block tile TF x TF (64, or 32 when 64-wide tiles would leave most of the
-// chip idle), 16 x 16 threads of (TF / 16)^2 outputs each.
-template <int TF, int EPI>
-__global__ __launch_bounds__(256) void gemm_tiled_f32(const float* __restrict__ A,
-                                                      const float* __restrict__ W, int M, int N,
-                                                      int K, float* __restrict__ out) {
-  constexpr int R = TF / 16;
-  __shared__ float As[TF_K][TF + 1];
-  __shared__ float Bs[TF_K][TF + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m0 = blockIdx.x * TF, n0 = blockIdx.y * TF;
-  float acc[R][R] = {};
-  for (int k0 = 0; k0 < K; k0 += TF_K) {
-    for (int q = threadIdx.x; q < TF * TF_K; q += 256) {
-      const int r = q / TF_K, c = q % TF_K;
-      const int m = m0 + r, n = n0 + r, k = k0 + c;
-      As[c][r] = (m < M && k < K) ? A[(size_t)m * K + k] : 0.f;
-      Bs[c][r] = (n < N && k < K) ? W[(size_t)n * K + k] : 0.f;
+template <int RT, int CT, int WM, int WN, int KS, int KC, int EPI>
+__global__ __launch_bounds__(WM * WN * KS * 64) void gemm_f32(const float* __restrict__ A,
+                                                              const float* __restrict__ W, int M,
+                                                              int N, int K,
+                                                              float* __restrict__ out) {
+  constexpr int NV = KC / 8;  // float4 per lane, row tile and chunk
+  constexpr bool kSwiglu = EPI == EPI_SWIGLU;
+  static_assert(!kSwiglu || CT == 2, "a gate and an up tile");
+  __shared__ f32x16_t red[KS > 1 ? (KS - 1) * WM * WN * RT * CT * 64 : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l32 = lane & 31, hi = lane >> 5;
+  const int ks = wave / (WM * WN), wt = wave % (WM * WN);
+  const int m0 = (blockIdx.x * WM + wt / WN) * RT * 32;
+  const int n0 = (blockIdx.y * WN + wt % WN) * (kSwiglu ? 1 : CT) * 32;
+  const float* ap[RT];
+  const float* wp[CT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+    ap[i] = A + (size_t)min(m0 + 32 * i + l32, M - 1) * K + hi * 4;
+#pragma unroll
+  for (int j = 0; j < CT; ++j) {
+    const int n = kSwiglu ? min(n0 + l32, N / 2 - 1) + j * (N / 2) : min(n0 + 32 * j + l32, N - 1);
+    wp[j] = W + (size_t)n * K + hi * 4;
+  }
+  f32x16_t acc[RT][CT];
+#pragma unroll
+  for (int i = 0; i < RT; ++i)
+#pragma unroll
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  // this wave's chunks of KC (K % KC == 0)
+  const int chunks = K / KC, c0 = chunks * ks / KS, c1 = chunks * (ks + 1) / KS;
+  f32x4_t ax[RT][NV], wx[CT][NV], ay[RT][NV], wy[CT][NV];
+  auto load = [&](f32x4_t (&a)[RT][NV], f32x4_t (&w)[CT][NV], int c) {
+    c = c < c1 ? c : c1 - 1;  // past the end: a valid chunk, never used
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) a[i][v] = *(const f32x4_t*)(ap[i] + (size_t)c * KC + 8 * v);
+#pragma unroll
+      for (int j = 0; j < CT; ++j) w[j][v] = *(const f32x4_any_t*)(wp[j] + (size_t)c * KC + 8 * v);
+    }
+  };
+  auto compute = [&](const f32x4_t (&a)[RT][NV], const f32x4_t (&w)[CT][NV]) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+          for (int j = 0; j < CT; ++j)
+            acc[i][j] = mfma32x32x2(a[i][v][e], w[j][v][e], acc[i][j]);
+  };
+  if (c0 < c1) {
+    load(ax, wx, c0);
+    int c = c0;
+    for (; c + 1 < c1; c += 2) {
+      load(ay, wy, c + 1);
+      compute(ax, wx);
+      load(ax, wx, c + 2);
+      compute(ay, wy);
+    }
+    if (c < c1) compute(ax, wx);
+  }
+  if constexpr (KS > 1) {
+    if (ks > 0) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < CT; ++j)
+          red[((((ks - 1) * WM * WN + wt) * RT + i) * CT + j) * 64 + lane] = acc[i][j];
     }
     __syncthreads();
+    if (ks > 0) return;
 #pragma unroll
-    for (int c = 0; c < TF_K; ++c) {
-      float a[R], b[R];
+    for (int q = 0; q < KS - 1; ++q)
 #pragma unroll
-      for (int i = 0; i < R; ++i) a[i] = As[c][ty * R + i];
+      for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int j = 0; j < R; ++j) b[j] = Bs[c][tx * R + j];
-#pragma unroll
-      for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < R; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
+        for (int j = 0; j < CT; ++j)
+          acc[i][j] += red[(((q * WM * WN + wt) * RT + i) * CT + j) * 64 + lane];
   }
+
+  // C layout: lane l holds column l % 32, value v row 8 (v / 4) + 4 (l / 32) + v % 4
 #pragma unroll
-  for (int i = 0; i < R; ++i) {
-    const int m = m0 + ty * R + i;
-    if (m >= M) continue;
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const int n = n0 + tx * R + j;
-      if (n >= N) continue;
-      if (EPI == EPI_RESID_ADD)
-        out[(size_t)m * N + n] += acc[i][j];
-      else
-        out[(size_t)m * N + n] = acc[i][j];
+    for (int v = 0; v < 16; ++v) {
+      const int m = m0 + 32 * i + 8 * (v >> 2) + 4 * hi + (v & 3);
+      if (m >= M) continue;
+      if constexpr (kSwiglu) {
+        const int n = n0 + l32;
+        if (n < N / 2) out[(size_t)m * (N / 2) + n] = silu_f(acc[i][0][v]) * acc[i][1][v];
+      } else {
+#pragma unroll
+        for (int j = 0; j < CT; ++j) {
+          const int n = n0 + 32 * j + l32;
+          if (n >= N) continue;
+          float* o = out + (size_t)m * N + n;
+          if (EPI == EPI_RESID_ADD)
+            *o += acc[i][j][v];
+          else
+            *o = acc[i][j][v];
+        }
+      }
     }
-  }
 }
 
-template <int TF>
-hipError_t launch_tiled_f32(Epilogue epi, const float* A, const float* W, int M, int N, int K,
-                            float* out, hipStream_t s) {
-  dim3 grid((M + TF - 1) / TF, (N + TF - 1) / TF);
-  if (epi == EPI_RESID_ADD)
-    gemm_tiled_f32<TF, EPI_RESID_ADD><<<grid, 256, 0, s>>>(A, W, M, N, K, out);
-  else if (epi == EPI_STORE_F32)
-    gemm_tiled_f32<TF, EPI_STORE_F32><<<grid, 256, 0, s>>>(A, W, M, N, K, out);
+// The largest tile that still gives every CU a block; below that 32 x 32
+// tiles with 4 or, where even those are few and K is long, 8 K ranges per
+// block. (SwiGLU: a 32-column tile is a gate and an up tile.)
+template <int EPI>
+hipError_t launch_gemm_f32(const float* A, const float* W, int M, int N, int K, float* out,
+                           hipStream_t s) {
+  constexpr bool kSwiglu = EPI == EPI_SWIGLU;
+  constexpr int CT = kSwiglu ? 2 : 1;
+  const int cols = kSwiglu ? N / 2 : N;
+  auto up = [](int v, int t) { return (v + t - 1) / t; };
+  auto tiles = [&](int tm, int tn) { return (long)up(M, tm) * up(cols, tn); };
+  constexpr int BN = kSwiglu ? 64 : 128;  // columns of the largest tile
+  if (tiles(128, BN) >= 256)
+    gemm_f32<2, 2, 2, 2, 1, 16, EPI><<<dim3(up(M, 128), up(cols, BN)), 256, 0, s>>>(A, W, M, N, K, out);
+  else if (tiles(64, 64) >= 256)
+    gemm_f32<1, CT, 2, 2, 2, 32, EPI><<<dim3(up(M, 64), up(cols, 64)), 512, 0, s>>>(A, W, M, N, K, out);
+  else if (tiles(32, 32) > 512 || K < 512)
+    gemm_f32<1, CT, 1, 1, 4, 32, EPI><<<dim3(up(M, 32), up(cols, 32)), 256, 0, s>>>(A, W, M, N, K, out);
   else
-    return hipErrorInvalidValue;
+    gemm_f32<1, CT, 1, 1, 8, 32, EPI><<<dim3(up(M, 32), up(cols, 32)), 512, 0, s>>>(A, W, M, N, K, out);
   return hipGetLastError();
 }
 
 // fp32 products of at most kGemvRows rows (decode steps in the fp32 mode):
 // one wave per output column, its lanes striding over K for every row, each
-// row's sum then reduced across the wave in a fixed order. On 64 x 64 tiles
-// such a product runs N / 64 workgroups over the whole of K (the tiny
-// shape's down projection: 4 workgroups, 95 us).
-constexpr int kGemvRows = 8;
+// row's sum then reduced across the wave in a fixed order: N waves, where
+// matrix tiles would be mostly padding and N / 32 blocks.
 
 template <int MR, int EPI>
 __global__ __launch_bounds__(256) void gemv_f32(const float* __restrict__ A,
@@ -1101,10 +1188,15 @@ hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int
     return hipErrorInvalidValue;
   }
   if (dt == DT_F32) {
-    const long tiles64 = (long)((M + 63) / 64) * ((N + 63) / 64);
-    if (tiles64 < 128)
-      return launch_tiled_f32<32>(epi, (const float*)A, (const float*)W, M, N, K, (float*)out, s);
-    return launch_tiled_f32<64>(epi, (const float*)A, (const float*)W, M, N, K, (float*)out, s);
+    if (K % 32 != 0) return hipErrorInvalidValue;
+    const float *a32 = (const float*)A, *w32 = (const float*)W;
+    if (epi == EPI_RESID_ADD)
+      return launch_gemm_f32<EPI_RESID_ADD>(a32, w32, M, N, K, (float*)out, s);
+    if (epi == EPI_STORE_F32)
+      return launch_gemm_f32<EPI_STORE_F32>(a32, w32, M, N, K, (float*)out, s);
+    if (epi == EPI_SWIGLU && N % 2 == 0)
+      return launch_gemm_f32<EPI_SWIGLU>(a32, w32, M, N, K, (float*)out, s);
+    return hipErrorInvalidValue;
   }
   if (N % 128 != 0 || K % 64 != 0) return hipErrorInvalidValue;
   // Three tilings: 256 x 256 and 192 x 256 (8 waves, one block per CU) and

@@ -16,6 +16,7 @@ enum Epilogue {
   EPI_STORE_F32 = 0,  // out (fp32, [M, N]) = acc
   EPI_RESID_ADD = 1,  // out (fp32 residual, [M, N]) += acc
   EPI_SWIGLU = 2,     // W = [gate (N/2 rows); up (N/2 rows)]; out (mode dtype, [M, N/2]) = silu(g) * u
+                      // (fp32: more than kGemvRows rows only)
   EPI_ROPE_Q = 3      // query columns, head_dim 128 (bf16 only): out (bf16, [M, N] row-major) =
                       // rotate-half RoPE of acc at the row's position (RopeRows)
 };
@@ -158,7 +159,9 @@ hipError_t gemm_skinny(const void* A, const void* W, int M, int N, int K, int sp
 // Needs N % 256 == 0 and K % (64 * splits) == 0.
 hipError_t gemm_split_k(const void* A, const void* W, int M, int N, int K, int splits, float* out,
                         hipStream_t s);
-// gemm: bf16 = LDS-tiled MFMA over packed A and W; fp32 = SIMT, row-major.
+// gemm: bf16 = LDS-tiled MFMA over packed A and W; fp32 = row-major, MFMA
+// tiles or, up to kGemvRows rows, one wave per output column.
+constexpr int kGemvRows = 8;
 hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int N, int K,
                 void* out, hipStream_t s, RopeRows rope = RopeRows{});
 
@@ -176,7 +179,8 @@ hipError_t attn_prefill(DType dt, const void* q, KVLayer kv, SegTables tabs,
                         const PrefillItem* items, int n_items, int n_q, void* out,
                         hipStream_t s);
 
-// fp32 mode: one wave per (token, head) over rows [t_begin, t_begin + n_tok).
+// fp32 mode: one workgroup per (up to 16 / G consecutive tokens, kv head) over
+// rows [t_begin, t_begin + n_tok), prefill and decode alike.
 hipError_t attn_f32(const float* q, KVLayer kv, SegTables tabs, const int32_t* tok_seq,
                     const int32_t* tok_pos, int t_begin, int n_tok, int n_q, float* out,
                     hipStream_t s);

@@ -723,8 +723,12 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
           }
         }
       } else {
-        L(STAGE_OP_GATE_UP, [&] { return gemm(dt, EPI_STORE_F32, h, w.w_gate_up, T, 2 * F, H, gu, ls); });
-        L(STAGE_OP_NORM, [&] { return swiglu_f32(gu, (float*)m, T, F, ls); });
+        if (T > kGemvRows) {
+          L(STAGE_OP_GATE_UP, [&] { return gemm(dt, EPI_SWIGLU, h, w.w_gate_up, T, 2 * F, H, m, ls); });
+        } else {
+          L(STAGE_OP_GATE_UP, [&] { return gemm(dt, EPI_STORE_F32, h, w.w_gate_up, T, 2 * F, H, gu, ls); });
+          L(STAGE_OP_NORM, [&] { return swiglu_f32(gu, (float*)m, T, F, ls); });
+        }
         L(STAGE_OP_DOWN, [&] { return gemm(dt, EPI_RESID_ADD, m, w.w_down, T, H, F, x, ls); });
       }
     }
