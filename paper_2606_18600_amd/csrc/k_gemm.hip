@@ -13,7 +13,9 @@
 //   split the gate-up GEMM applies SwiGLU in its epilogue. 65-128 rows run
 //   on 8 waves (gemm_skinny8_bf16); products split over K run on 8 waves
 //   over two weight groups and four k parts (gemm_skinny_kp_bf16), which
-//   halves the number of partial planes for the same number of blocks.
+//   halves the number of partial planes for the same number of blocks. At
+//   most 32 rows of a narrow product run on gemm_stream_bf16, which splits K
+//   over the waves of a block.
 // * gemm_tiled_bf16: many rows (prefill, mixed steps), compute-bound.
 //   256 x 256 (8 waves of 64 x 128), 192 x 256 or 128 x 128 block tiles;
 //   weight fragments copied HBM -> LDS with direct loads (64-wide k steps,
@@ -381,11 +383,12 @@ void gemm_skinny8_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict__ 
 // finishing MR = ceil(MT / KP) m-tiles. With two groups per block a launch
 // needs half the K ranges of the four-group kernels for the same number of
 // blocks, so the fp32 partial planes it writes, and its consumer reads,
-// halve too.
-template <int MT, int GW>
+// halve too. With one K range and SK_SWIGLU it is the gate-up product of
+// FFN shares too narrow for the four-group kernels.
+template <int MT, int GW, int EPI>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
 void gemm_skinny_kp_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N,
-                         int K, int kb_len, float* __restrict__ out, bool rotate) {
+                         int K, int kb_len, void* __restrict__ out, bool rotate) {
   constexpr int KP = 8 / GW;
   constexpr int AF = MT * KP;                        // A fragments per step
   constexpr int NA = (AF + 7) / 8;                   // A copies per wave and step
@@ -514,7 +517,7 @@ void gemm_skinny_kp_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict_
   if (!live) return;
 
   // each wave stores the m-tiles it finished, as in gemm_skinny_bf16
-  float* part = out + (size_t)blockIdx.y * M * N;
+  float* part = (float*)out + (size_t)blockIdx.y * M * N;
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     if (i / MR != kp) continue;
@@ -522,8 +525,132 @@ void gemm_skinny_kp_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict_
     for (int r = 0; r < 4; ++r) {
       const int m = i * 16 + (lane >> 4) * 4 + r;
       if (m >= M) continue;
+      if constexpr (EPI == SK_PARTIAL) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) part[(size_t)m * N + g * 64 + j * 16 + r16] = acc[i][j][r];
+        for (int j = 0; j < 4; ++j) part[(size_t)m * N + g * 64 + j * 16 + r16] = acc[i][j][r];
+      } else {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          ((bf16_t*)out)[packed_a_offset(m, g * 32 + j * 16 + r16, N / 2)] =
+              f32_to_bf16(silu_f(acc[i][j][r]) * acc[i][j + 2][r]);
+      }
+    }
+  }
+}
+
+// At most 32 rows on 8 waves that share nothing until the end: a block owns NF
+// of a group's 4 weight fragments per k tile (NF = 4: 64 columns; NF = 2: 16
+// gate and the 16 matching up columns, or 32 adjacent ones) over one K range,
+// and wave w streams k tiles w, w + 8, ... of it, weights and the MT
+// activation fragments alike, straight into registers, kDepth tiles ahead.
+// With one group per block no two waves of it need the same A fragment, so
+// there is nothing to stage in LDS and no barrier per step; the price, A read
+// once per 64 (32) columns, is small next to the weights while M is (rows past
+// M are not loaded). Splitting K within the block instead of over blocks is
+// what narrow products need (few groups: one rank's heads or FFN share, small
+// models): a fraction of the fp32 planes, and a SwiGLU product that needs no
+// planes and no second pass at all. Measured over the kernels above at 16
+// rows: [8192, 1024] 6.3 -> 5.5 us and 4 -> 2 planes, [1280, 8192] 6.3 -> 6.2
+// us and 22 -> 6 planes, [8192, 8192] 22.8 -> 22.1 us (6.1 TB/s) and 4 -> 2.
+constexpr int kStreamDepth = 4;
+
+template <int MT, int NF, int EPI>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+void gemm_stream_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int N,
+                      int K, int kb_len, void* __restrict__ out) {
+  constexpr int NW = 8, DEPTH = kStreamDepth;
+  __shared__ f32x4_t red[NW][MT * NF * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r16 = lane & 15;
+  const int g = blockIdx.x / (4 / NF), part = blockIdx.x % (4 / NF);
+  const int KT = K / 32;
+  const int kt0 = blockIdx.y * (kb_len / 32) + wave;
+  const int kt1 = min((int)(blockIdx.y + 1) * (kb_len / 32), KT);
+  const int n = kt0 < kt1 ? (kt1 - kt0 + NW - 1) / NW : 0;  // this wave's k tiles
+  // fragment f of the block is the group's fragment frag(f)
+  auto frag = [&](int f) {
+    if (NF == 4) return f;
+    return EPI == SK_SWIGLU ? part + 2 * f : 2 * part + f;
+  };
+  const bf16_t* wp = W + ((size_t)g * KT + kt0) * 4 * 512 + lane * 8;
+  const bf16_t* ap = A + (size_t)kt0 * 512 + lane * 8;
+
+  f32x4_t acc[MT][NF];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) acc[i][f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  u32x4_t w[DEPTH][NF], a[DEPTH][MT];
+  auto load = [&](int d, int t) {
+    t = t < n ? t : n - 1;  // past the end: a valid tile, never used
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+      w[d][f] = __builtin_nontemporal_load(
+          (const u32x4_t*)(wp + ((size_t)t * NW * 4 + frag(f)) * 512));
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      a[d][i] = i * 16 + r16 < M ? ldg128(ap + ((size_t)i * KT + (size_t)t * NW) * 512)
+                                 : u32x4_t{0u, 0u, 0u, 0u};
+  };
+  auto compute = [&](int d) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int f = 0; f < NF; ++f) acc[i][f] = mfma16x16x32(a[d][i], w[d][f], acc[i][f]);
+  };
+  if (n > 0) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) load(d, d);
+    int t = 0;
+    for (; t + DEPTH <= n; t += DEPTH) {
+#pragma unroll
+      for (int d = 0; d < DEPTH; ++d) {
+        __builtin_amdgcn_sched_barrier(0);
+        compute(d);
+        __builtin_amdgcn_sched_barrier(0);
+        load(d, t + DEPTH + d);
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH - 1; ++d)
+      if (t + d < n) compute(d);
+  }
+
+  // the waves' sums, in wave order
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) red[wave][(i * NF + f) * 64 + lane] = acc[i][f];
+  __syncthreads();
+  auto total = [&](int i, int f, int l) {
+    f32x4_t v = red[0][(i * NF + f) * 64 + l];
+#pragma unroll
+    for (int q = 1; q < NW; ++q) v += red[q][(i * NF + f) * 64 + l];
+    return v;
+  };
+  if (EPI == SK_PARTIAL) {
+    float* o = (float*)out + (size_t)blockIdx.y * M * N;
+    for (int e = threadIdx.x; e < MT * NF * 64; e += NW * 64) {
+      const int l = e & 63, f = (e >> 6) % NF, i = (e >> 6) / NF;
+      const f32x4_t v = total(i, f, l);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = i * 16 + (l >> 4) * 4 + r;
+        if (m < M) o[(size_t)m * N + g * 64 + frag(f) * 16 + (l & 15)] = v[r];
+      }
+    }
+  } else {
+    const int F = N / 2;
+    for (int e = threadIdx.x; e < MT * (NF / 2) * 64; e += NW * 64) {
+      const int l = e & 63, f = (e >> 6) % (NF / 2), i = (e >> 6) / (NF / 2);
+      const f32x4_t vg = total(i, f, l), vu = total(i, f + NF / 2, l);
+      const int c = g * 32 + frag(f) * 16 + (l & 15);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = i * 16 + (l >> 4) * 4 + r;
+        if (m < M)
+          ((bf16_t*)out)[packed_a_offset(m, c, F)] = f32_to_bf16(silu_f(vg[r]) * vu[r]);
+      }
     }
   }
 }
@@ -1053,12 +1180,31 @@ bool skinny8_enabled() {
 }
 
 template <int MT>
+hipError_t launch_stream(const bf16_t* a, const bf16_t* w, int M, int N, int K, int kb_len,
+                         int splits, bool halves, bool swiglu, void* out, hipStream_t s) {
+  const dim3 grid(N / 64 * (halves ? 2 : 1), splits);
+  if (swiglu && halves)
+    gemm_stream_bf16<MT, 2, SK_SWIGLU><<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len, out);
+  else if (swiglu)
+    gemm_stream_bf16<MT, 4, SK_SWIGLU><<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len, out);
+  else if (halves)
+    gemm_stream_bf16<MT, 2, SK_PARTIAL><<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len, out);
+  else
+    gemm_stream_bf16<MT, 4, SK_PARTIAL><<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len, out);
+  return hipGetLastError();
+}
+
+template <int MT>
 hipError_t launch_skinny_kp(const bf16_t* a, const bf16_t* w, int M, int N, int K, int kb_len,
-                            int splits, void* out, hipStream_t s) {
+                            int splits, bool swiglu, void* out, hipStream_t s) {
   const int groups = N / 64;
   dim3 grid((groups + kSkinnyKpGroups - 1) / kSkinnyKpGroups, splits);
-  gemm_skinny_kp_bf16<MT, kSkinnyKpGroups><<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len,
-                                                                 (float*)out, skinny_rot());
+  if (swiglu)
+    gemm_skinny_kp_bf16<MT, kSkinnyKpGroups, SK_SWIGLU>
+        <<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len, out, skinny_rot());
+  else
+    gemm_skinny_kp_bf16<MT, kSkinnyKpGroups, SK_PARTIAL>
+        <<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len, out, skinny_rot());
   return hipGetLastError();
 }
 
@@ -1104,22 +1250,30 @@ hipError_t gemm_skinny(const void* A, const void* W, int M, int N, int K, int sp
     return hipErrorInvalidValue;
   const bf16_t* a = (const bf16_t*)A;
   const bf16_t* w = (const bf16_t*)W;
-  if (skinny_kp_used(K, splits, swiglu)) {
-    const int kb = skinny_kp_kb_len(K, splits);
-    if ((K + kb - 1) / kb != splits) return hipErrorInvalidValue;  // every split non-empty
+  const int kb =
+      skinny_kp_used(K, splits, swiglu) ? skinny_kp_kb_len(K, splits) : skinny_kb_len(K, splits);
+  if ((K + kb - 1) / kb != splits) return hipErrorInvalidValue;  // every split must be non-empty
+  if (const int frags = stream_fragments(M, N, K, splits, swiglu)) {
+    if (M <= 16) return launch_stream<1>(a, w, M, N, K, kb, splits, frags == 2, swiglu, out, s);
+    return launch_stream<2>(a, w, M, N, K, kb, splits, frags == 2, swiglu, out, s);
+  }
+  // A SwiGLU product whose groups, four to a block, leave a third of the CUs
+  // without one (a rank's half of a wide FFN) runs two groups to a block:
+  // a three-layer decode step of 64 rows at N = 28672, K = 8192 went from 738
+  // to 625 us with it, of 4 rows from 593 to 538 us.
+  if (skinny_kp_used(K, splits, swiglu) ||
+      (swiglu && N / 64 <= 512 && K % 128 == 0 && skinny_kp_enabled())) {
     switch ((M + 15) / 16) {
-      case 1: return launch_skinny_kp<1>(a, w, M, N, K, kb, splits, out, s);
-      case 2: return launch_skinny_kp<2>(a, w, M, N, K, kb, splits, out, s);
-      case 3: return launch_skinny_kp<3>(a, w, M, N, K, kb, splits, out, s);
-      case 4: return launch_skinny_kp<4>(a, w, M, N, K, kb, splits, out, s);
-      case 5: return launch_skinny_kp<5>(a, w, M, N, K, kb, splits, out, s);
-      case 6: return launch_skinny_kp<6>(a, w, M, N, K, kb, splits, out, s);
-      case 7: return launch_skinny_kp<7>(a, w, M, N, K, kb, splits, out, s);
-      default: return launch_skinny_kp<8>(a, w, M, N, K, kb, splits, out, s);
+      case 1: return launch_skinny_kp<1>(a, w, M, N, K, kb, splits, swiglu, out, s);
+      case 2: return launch_skinny_kp<2>(a, w, M, N, K, kb, splits, swiglu, out, s);
+      case 3: return launch_skinny_kp<3>(a, w, M, N, K, kb, splits, swiglu, out, s);
+      case 4: return launch_skinny_kp<4>(a, w, M, N, K, kb, splits, swiglu, out, s);
+      case 5: return launch_skinny_kp<5>(a, w, M, N, K, kb, splits, swiglu, out, s);
+      case 6: return launch_skinny_kp<6>(a, w, M, N, K, kb, splits, swiglu, out, s);
+      case 7: return launch_skinny_kp<7>(a, w, M, N, K, kb, splits, swiglu, out, s);
+      default: return launch_skinny_kp<8>(a, w, M, N, K, kb, splits, swiglu, out, s);
     }
   }
-  const int kb = skinny_kb_len(K, splits);
-  if ((K + kb - 1) / kb != splits) return hipErrorInvalidValue;  // every split must be non-empty
   switch ((M + 15) / 16) {
     case 1: return launch_skinny<1>(a, w, M, N, K, kb, swiglu, out, s);
     case 2: return launch_skinny<2>(a, w, M, N, K, kb, swiglu, out, s);

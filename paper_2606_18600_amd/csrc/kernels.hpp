@@ -152,6 +152,23 @@ int skinny_kp_kb_len(int K, int splits);
 // K splits for the k-part kernel: as many as keep the launch at
 // <= target_blocks blocks (at most max_splits).
 int skinny_kp_splits(int N, int K, int target_blocks, int max_splits = kSkinnyMaxSplits);
+// Products of at most kStreamRows rows whose weights are narrow run on the
+// kernel that splits K over the waves of a block (gemm_stream_bf16): whole
+// 64-column groups (4 fragments per k tile) or half groups (2) of at most
+// kStreamBlocks blocks, one per CU. stream_fragments says which of the two a
+// product of these splits takes (0: neither), stream_splits how many K ranges
+// such a product should be given (0: use the other kernels' plan): halves up
+// to 64 groups, so that the planes its consumer sums are fewest; whole groups
+// above. Whole groups with more than kStreamMaxRange of K per block stay on
+// the k-part kernel (8192 x 28672 at 16 rows: 72.8 us against 70.0; at 8192 x
+// 7168 19.5 against 20.3, with half the planes). SwiGLU (one K range) goes by
+// the second pass it saves: [14336, 8192] at 16 rows 42.0 us against 37.6 and
+// a reduction of 5; [7168, 8192] in halves 21.1 against 20.3 and 4.6.
+constexpr int kStreamRows = 32;
+constexpr int kStreamBlocks = 256;
+constexpr int kStreamMaxRange = 4096;
+int stream_fragments(int M, int N, int K, int splits, bool swiglu);
+int stream_splits(int N, int K, int max_splits, bool swiglu);
 hipError_t gemm_skinny(const void* A, const void* W, int M, int N, int K, int splits, bool swiglu,
                        void* out, hipStream_t s);
 // bf16 LDS-tiled product split over K: `splits` fp32 partial planes

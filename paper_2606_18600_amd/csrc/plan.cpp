@@ -47,6 +47,29 @@ int skinny_kp_splits(int N, int K, int target_blocks, int max_splits) {
   return (K + kb - 1) / kb;
 }
 
+int stream_fragments(int M, int N, int K, int splits, bool swiglu) {
+  if (M > kStreamRows) return 0;
+  const int groups = N / 64;
+  if (2 * groups * splits <= kStreamBlocks) return 2;
+  if (groups * splits > kStreamBlocks) return 0;
+  return swiglu || K / splits <= kStreamMaxRange ? 4 : 0;
+}
+
+int stream_splits(int N, int K, int max_splits, bool swiglu) {
+  const int groups = N / 64;
+  if (groups > kStreamBlocks) return 0;
+  const int per = groups <= 64 ? 2 : 1;  // blocks per group and K range
+  int s = 1;
+  if (!swiglu) {
+    s = std::max(1, std::min({kStreamBlocks / (per * groups), max_splits, K / 256}));
+    const int kb = K % 128 == 0 ? skinny_kp_kb_len(K, s) : skinny_kb_len(K, s);
+    s = (K + kb - 1) / kb;
+  }
+  const int frags = stream_fragments(1, N, K, s, swiglu);
+  const int blocks = groups * s * (frags == 2 ? 2 : 1);
+  return frags && (blocks * 10 >= kStreamBlocks * 7 || K <= 2048) ? s : 0;
+}
+
 int prefill_item_positions(DType dt, int group) {
   (void)dt;
   return kPrefillRows / group;

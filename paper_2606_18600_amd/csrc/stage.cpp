@@ -111,6 +111,10 @@ struct stage {
   int skinny_rows = 0;  // steps with at most this many tokens use split-K GEMMs
   // K splits of the four split-K GEMMs (QKV, O, gate-up, down)
   int s_qkv = 1, s_o = 1, s_gu = 1, s_down = 1;
+  // ... and of steps of at most kStreamRows rows (never more than the above;
+  // gate-up: whether SwiGLU then needs no K splits)
+  int few_qkv = 1, few_o = 1, few_down = 1;
+  bool few_gu = false;
   // decode attention waves to aim for: one resident round (the kernel runs
   // two waves per SIMD, 2048 on the chip) with slack for per-sequence
   // rounding of the split sizes
@@ -546,6 +550,10 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
   const int np = pf ? pf->num_seqs : 0, nd = dc ? dc->num_seqs : 0;
   const DType dt = (DType)c.dtype;
   const bool skinny = dt == DT_BF16 && T <= st->skinny_rows;
+  const bool few = T <= kStreamRows;
+  const int sk_qkv = few ? st->few_qkv : st->s_qkv, sk_o = few ? st->few_o : st->s_o,
+            sk_down = few ? st->few_down : st->s_down;
+  const bool sk_gu_fused = st->s_gu == 1 || (few && st->few_gu);
 
   // metadata: host build in a pinned staging slot, one async upload
   int slot = 0;
@@ -619,9 +627,9 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
       }
       if (skinny) {
         const size_t plane = (size_t)T * qkvw;
-        qsrc = ProjSrc{qkv, qkvw, st->s_qkv, plane};
-        kvsrc = ProjSrc{qkv + qw, qkvw, st->s_qkv, plane};
-        L(STAGE_OP_QKV, [&] { return gemm_skinny(h, w.w_qkv, T, qkvw, H, st->s_qkv, false, qkv, ls); });
+        qsrc = ProjSrc{qkv, qkvw, sk_qkv, plane};
+        kvsrc = ProjSrc{qkv + qw, qkvw, sk_qkv, plane};
+        L(STAGE_OP_QKV, [&] { return gemm_skinny(h, w.w_qkv, T, qkvw, H, sk_qkv, false, qkv, ls); });
       } else if (mq > 0) {
         const size_t plane = (size_t)T * qkvw;
         qsrc = ProjSrc{qkv, qkvw, mq, plane};
@@ -676,8 +684,8 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
       }
 
       if (skinny) {
-        L(STAGE_OP_O, [&] { return gemm_skinny(attn, w.w_o, T, H, qw, st->s_o, false, part_x, ls); });
-        pending = Partials{part_x, st->s_o};
+        L(STAGE_OP_O, [&] { return gemm_skinny(attn, w.w_o, T, H, qw, sk_o, false, part_x, ls); });
+        pending = Partials{part_x, sk_o};
       } else if (mo > 0) {
         L(STAGE_OP_O, [&] { return gemm_split_k(attn, w.w_o, T, H, qw, mo, part_x, ls); });
         pending = Partials{part_x, mo};
@@ -695,7 +703,7 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
       pending = Partials{nullptr, 0};
 
       if (skinny) {
-        if (st->s_gu == 1) {
+        if (sk_gu_fused) {
           L(STAGE_OP_GATE_UP, [&] { return gemm_skinny(h, w.w_gate_up, T, 2 * F, H, 1, true, m, ls); });
         } else {
           L(STAGE_OP_GATE_UP, [&] {
@@ -705,8 +713,8 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
             return swiglu_reduce_bf16(Partials{gu, st->s_gu}, (uint16_t*)m, T, F, ls);
           });
         }
-        L(STAGE_OP_DOWN, [&] { return gemm_skinny(m, w.w_down, T, H, F, st->s_down, false, part_x, ls); });
-        pending = Partials{part_x, st->s_down};
+        L(STAGE_OP_DOWN, [&] { return gemm_skinny(m, w.w_down, T, H, F, sk_down, false, part_x, ls); });
+        pending = Partials{part_x, sk_down};
       } else if (dt == DT_BF16) {
         L(STAGE_OP_GATE_UP, [&] { return gemm(dt, EPI_SWIGLU, h, w.w_gate_up, T, 2 * F, H, m, ls); });
         if (md > 0) {
@@ -734,7 +742,7 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
     }
   };
   // what the last layer leaves for the output cast
-  const Partials tail = skinny   ? Partials{part_x, st->s_down}
+  const Partials tail = skinny   ? Partials{part_x, sk_down}
                         : md > 0 ? Partials{part_x, md}
                         : rd > 0 ? Partials{part_x, st->s_down, Td}
                                  : Partials{nullptr, 0};
@@ -823,6 +831,14 @@ stage_status stage_create(const stage_model_config* cfg, int32_t layer_begin, in
     st->s_o = splits_for(H, qw, kSkinnyMaxSplits);
     st->s_gu = splits_for(2 * F, H, kSkinnyMaxSplits);
     st->s_down = splits_for(H, F, kSkinnyMaxSplits);
+    auto few_for = [&](int N, int K, int planned) {
+      const int f = stream_splits(N, K, planned, false);
+      return f ? f : planned;
+    };
+    st->few_qkv = few_for(qkvw, H, st->s_qkv);
+    st->few_o = few_for(H, qw, st->s_o);
+    st->few_down = few_for(H, F, st->s_down);
+    st->few_gu = stream_splits(2 * F, H, 1, true) == 1;
     st->attn_waves = std::max(64, env_int("STAGE_ATTN_WAVES", 1600));
     st->attn_scale = env_int("STAGE_ATTN_SCALE", 1) != 0;
     st->row_tail_on = env_int("STAGE_ROW_TAIL", 1) != 0;
