@@ -161,13 +161,17 @@ __global__ __launch_bounds__(256) void attn_decode_bf16(const bf16_t* __restrict
                                                         SegTables tabs,
                                                         const DecodeItem* __restrict__ items,
                                                         const int32_t* __restrict__ order,
-                                                        int n_q, float* __restrict__ part_o,
+                                                        int n_items, int n_q,
+                                                        float* __restrict__ part_o,
                                                         float* __restrict__ part_ml) {
   const int lane = threadIdx.x & 63;
   const int kvh = blockIdx.y * 4 + (threadIdx.x >> 6);
   if (kvh >= n_kv) return;
   const int idx = order[blockIdx.x];
   const DecodeItem it = items[idx];
+  // items of one token are adjacent, from key 0 on: alone if the next item
+  // starts at key 0 again
+  const bool alone = it.k0 == 0 && (idx + 1 == n_items || items[idx + 1].k0 == 0);
   const int G = n_q / n_kv;
   const int row = lane & 15;  // query head within the group
   const bool row_ok = row < G;
@@ -237,6 +241,19 @@ __global__ __launch_bounds__(256) void attn_decode_bf16(const bf16_t* __restrict
   }
 
   if (!row_ok) return;
+  if (alone) {
+    const float inv = 1.0f / st.l;
+    bf16_t* out = (bf16_t*)tabs.attn_out;
+    const int col = (kvh * G + row) * D + (lane >> 4) * 4;
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) {
+      u32x2_t w;
+      w[0] = pack_bf16x2(oacc[t][0] * inv, oacc[t][1] * inv);
+      w[1] = pack_bf16x2(oacc[t][2] * inv, oacc[t][3] * inv);
+      *(u32x2_t*)(out + packed_a_offset(it.tok, col + t * 16, n_q * D)) = w;
+    }
+    return;
+  }
   const size_t ob = ((size_t)idx * n_q + kvh * G + row);
   float* po = part_o + ob * D;
 #pragma unroll
@@ -248,33 +265,39 @@ __global__ __launch_bounds__(256) void attn_decode_bf16(const bf16_t* __restrict
   }
 }
 
-// Combine the key splits of each decode token: one wave per (token, kv
-// head). Lane l serves query head row r = l / LPR of the group and DPL
-// consecutive d values (a multiple of 4).
-template <int D, int G>
-__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ part_o,
-                                                         const float* __restrict__ part_ml,
-                                                         const int32_t* __restrict__ item_start,
-                                                         const int32_t* __restrict__ tok_rows,
-                                                         int n_q, int n_kv,
-                                                         bf16_t* __restrict__ out) {
+// Combine the key splits of each decode token. WPT waves per (token, kv
+// head): wave w takes splits 4 w .. 4 w + 3, then the 4 WPT further on. Lane l
+// serves query head row l / LPR of the group and DPL consecutive d values (a
+// multiple of 4). Bound by latency: a wave's chain is one memory round trip
+// per 4 splits, so batches that are small enough to leave CUs free (and whose
+// tokens then have many splits) share the chain between waves: one token of 8
+// kv heads, 11.7 us for 32 splits with one wave each, 6.8 for 55 with eight;
+// 32 tokens of 14 splits and one kv head 6.1 -> 4.2.
+template <int D, int G, int WPT>
+__global__ __launch_bounds__(WPT == 1 ? 256 : WPT * 64) void attn_merge_kernel(
+    const float* __restrict__ part_o, const float* __restrict__ part_ml,
+    const int32_t* __restrict__ item_start, const int32_t* __restrict__ tok_rows, int n_q,
+    int n_kv, bf16_t* __restrict__ out) {
   constexpr int LPR = (64 / G) < (D / 4) ? (64 / G) : (D / 4);  // lanes per head row
   constexpr int DPL = D / LPR;                                    // d values per lane
+  __shared__ float2 s_ml[WPT][G];
+  __shared__ float4 s_o[WPT > 1 ? WPT : 1][WPT > 1 ? G * D / 4 : 1];
   const int t = blockIdx.x;
-  const int kvh = blockIdx.y * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (kvh >= n_kv || lane >= G * LPR) return;
-  const int h = kvh * G + lane / LPR;
-  const int d0 = (lane % LPR) * DPL;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int kvh = WPT > 1 ? blockIdx.y : blockIdx.y * 4 + wave;
   const int i0 = item_start[t], i1 = item_start[t + 1];
+  if (i1 - i0 == 1) return;  // written by its item
+  const bool on = lane < G * LPR;
+  if (WPT == 1 && (kvh >= n_kv || !on)) return;
+  const int h = kvh * G + (on ? lane / LPR : 0);
+  const int d0 = (lane % LPR) * DPL;
   // Online merge over chunks of 4 splits: a chunk's loads are all issued
-  // before any is used (indices past the last split are clamped and masked),
-  // so a token with up to 4 splits costs one memory round trip.
+  // before any is used (indices past the last split are clamped and masked).
   float M = -INFINITY, L = 0.f;
   float4 o[DPL / 4];
 #pragma unroll
   for (int c = 0; c < DPL / 4; ++c) o[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int i = i0; i < i1; i += 4) {
+  for (int i = i0 + (WPT > 1 ? 4 * wave : 0); i < i1; i += 4 * WPT) {
     float mu[4], lu[4];
     float4 v[4][DPL / 4];
 #pragma unroll
@@ -313,14 +336,49 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
     }
     M = cm;
   }
-  const float inv = 1.0f / L;
   const int row = tok_rows[t], K = n_q * D;
+  if constexpr (WPT == 1) {
+    const float inv = 1.0f / L;
 #pragma unroll
-  for (int c = 0; c < DPL / 4; ++c) {
-    u32x2_t wv;
-    wv[0] = pack_bf16x2(o[c].x * inv, o[c].y * inv);
-    wv[1] = pack_bf16x2(o[c].z * inv, o[c].w * inv);
-    *(u32x2_t*)(out + packed_a_offset(row, h * D + d0 + 4 * c, K)) = wv;
+    for (int c = 0; c < DPL / 4; ++c) {
+      u32x2_t wv;
+      wv[0] = pack_bf16x2(o[c].x * inv, o[c].y * inv);
+      wv[1] = pack_bf16x2(o[c].z * inv, o[c].w * inv);
+      *(u32x2_t*)(out + packed_a_offset(row, h * D + d0 + 4 * c, K)) = wv;
+    }
+  } else {
+    // the waves' parts; a wave without splits has M = -inf and weight 0
+    // (wave 0 always has some, so the common maximum is one of the splits')
+    const int r = lane / LPR;
+    if (on && lane % LPR == 0) s_ml[wave][r] = make_float2(M, L);
+    if (on) {
+#pragma unroll
+      for (int c = 0; c < DPL / 4; ++c) s_o[wave][(r * D + d0) / 4 + c] = o[c];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < G * D / 4; e += WPT * 64) {
+      const int er = e / (D / 4);
+      float cm = s_ml[0][er].x;
+#pragma unroll
+      for (int w = 1; w < WPT; ++w) cm = fmaxf(cm, s_ml[w][er].x);
+      float l = 0.f;
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int w = 0; w < WPT; ++w) {
+        const float f = exp2f(s_ml[w][er].x - cm);
+        l += f * s_ml[w][er].y;
+        const float4 b = s_o[w][e];
+        a.x += f * b.x;
+        a.y += f * b.y;
+        a.z += f * b.z;
+        a.w += f * b.w;
+      }
+      const float inv = 1.0f / l;
+      u32x2_t wv;
+      wv[0] = pack_bf16x2(a.x * inv, a.y * inv);
+      wv[1] = pack_bf16x2(a.z * inv, a.w * inv);
+      *(u32x2_t*)(out + packed_a_offset(row, kvh * G * D + 4 * e, K)) = wv;
+    }
   }
 }
 
@@ -788,26 +846,43 @@ hipError_t attn_decode(DType dt, const void* q, KVLayer kv, SegTables tabs,
   dim3 grid(n_items, (kv.n_kv + 3) / 4);
   if (kv.head_dim == 128)
     attn_decode_bf16<128><<<grid, 256, 0, s>>>((const bf16_t*)q, (const bf16_t*)kv.base, kv.n_kv,
-                                               tabs, items, order, n_q, part_o, part_ml);
+                                               tabs, items, order, n_items, n_q, part_o, part_ml);
   else if (kv.head_dim == 64)
     attn_decode_bf16<64><<<grid, 256, 0, s>>>((const bf16_t*)q, (const bf16_t*)kv.base, kv.n_kv,
-                                              tabs, items, order, n_q, part_o, part_ml);
+                                              tabs, items, order, n_items, n_q, part_o, part_ml);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+// Waves per (token, kv head): one while these alone fill the chip's SIMDs,
+// then as many as keep the launch near one wave per SIMD.
+template <int D, int G>
+static void launch_merge_g(const float* part_o, const float* part_ml, const int32_t* starts,
+                           const int32_t* rows, int n_tok, int n_q, int n_kv, bf16_t* out,
+                           hipStream_t s) {
+  const int pairs = n_tok * n_kv;
+  if (pairs > 256)
+    attn_merge_kernel<D, G, 1><<<dim3(n_tok, (n_kv + 3) / 4), 256, 0, s>>>(part_o, part_ml, starts,
+                                                                            rows, n_q, n_kv, out);
+  else if (pairs > 128 || G == 16)  // (G = 16 and 8 waves: more than 64 KB of LDS)
+    attn_merge_kernel<D, G, 4><<<dim3(n_tok, n_kv), 256, 0, s>>>(part_o, part_ml, starts, rows,
+                                                                 n_q, n_kv, out);
+  else
+    attn_merge_kernel<D, G, G == 16 ? 4 : 8><<<dim3(n_tok, n_kv), (G == 16 ? 4 : 8) * 64, 0, s>>>(
+        part_o, part_ml, starts, rows, n_q, n_kv, out);
 }
 
 template <int D>
 static hipError_t launch_merge(const float* part_o, const float* part_ml, const int32_t* starts,
                                const int32_t* rows, int n_tok, int n_q, int n_kv, bf16_t* out,
                                hipStream_t s) {
-  dim3 grid(n_tok, (n_kv + 3) / 4);
   switch (n_q / n_kv) {
-    case 1: attn_merge_kernel<D, 1><<<grid, 256, 0, s>>>(part_o, part_ml, starts, rows, n_q, n_kv, out); break;
-    case 2: attn_merge_kernel<D, 2><<<grid, 256, 0, s>>>(part_o, part_ml, starts, rows, n_q, n_kv, out); break;
-    case 4: attn_merge_kernel<D, 4><<<grid, 256, 0, s>>>(part_o, part_ml, starts, rows, n_q, n_kv, out); break;
-    case 8: attn_merge_kernel<D, 8><<<grid, 256, 0, s>>>(part_o, part_ml, starts, rows, n_q, n_kv, out); break;
-    case 16: attn_merge_kernel<D, 16><<<grid, 256, 0, s>>>(part_o, part_ml, starts, rows, n_q, n_kv, out); break;
+    case 1: launch_merge_g<D, 1>(part_o, part_ml, starts, rows, n_tok, n_q, n_kv, out, s); break;
+    case 2: launch_merge_g<D, 2>(part_o, part_ml, starts, rows, n_tok, n_q, n_kv, out, s); break;
+    case 4: launch_merge_g<D, 4>(part_o, part_ml, starts, rows, n_tok, n_q, n_kv, out, s); break;
+    case 8: launch_merge_g<D, 8>(part_o, part_ml, starts, rows, n_tok, n_q, n_kv, out, s); break;
+    case 16: launch_merge_g<D, 16>(part_o, part_ml, starts, rows, n_tok, n_q, n_kv, out, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -32,13 +32,16 @@ struct RopeRows {
 };
 
 // Block tables of the (at most) two segments of a step: sequences
-// [0, nseq0) read table 0, sequences [nseq0, ...) read table 1.
+// [0, nseq0) read table 0, sequences [nseq0, ...) read table 1. attn_out
+// (bf16 mode): the packed attention output, where decode attention writes the
+// row of a token with a single key split itself.
 struct SegTables {
   const int32_t* bt0;
   int32_t stride0;
   int32_t nseq0;
   const int32_t* bt1;
   int32_t stride1;
+  void* attn_out = nullptr;
 };
 
 // KV cache geometry of one layer: [num_blocks][n_kv][2][block * d]; plane 0
@@ -162,8 +165,9 @@ int skinny_kp_splits(int N, int K, int target_blocks, int max_splits = kSkinnyMa
 // above. Whole groups with more than kStreamMaxRange of K per block stay on
 // the k-part kernel (8192 x 28672 at 16 rows: 72.8 us against 70.0; at 8192 x
 // 7168 19.5 against 20.3, with half the planes). SwiGLU (one K range) goes by
-// the second pass it saves: [14336, 8192] at 16 rows 42.0 us against 37.6 and
-// a reduction of 5; [7168, 8192] in halves 21.1 against 20.3 and 4.6.
+// the second pass it saves: [14336, 8192] at 16 rows 37.6 us against 37.5 and
+// a reduction of 5; [7168, 8192] in halves 21.1 against 20.3 and 4.6; and up
+// to 16 rows it takes two blocks per CU ([28672, 8192] 72.3 us against 74.4).
 constexpr int kStreamRows = 32;
 constexpr int kStreamBlocks = 256;
 constexpr int kStreamMaxRange = 4096;
@@ -182,11 +186,14 @@ constexpr int kGemvRows = 8;
 hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int N, int K,
                 void* out, hipStream_t s, RopeRows rope = RopeRows{});
 
-// Decode attention: workgroup b takes item order[b] (the host's dispatch
-// order); partials are written at the item's own index.
+// Decode attention: items are taken in the host's dispatch order (order[0]
+// first). An item that holds all keys of its token writes the finished row to
+// tabs.attn_out; the others write partials at their own index.
 hipError_t attn_decode(DType dt, const void* q, KVLayer kv, SegTables tabs,
                        const DecodeItem* items, const int32_t* order, int n_items, int n_q,
                        float* part_o, float* part_ml, hipStream_t s);
+// Combines the partials of the tokens with several items (n_tok tokens in
+// all; those with a single item are left alone).
 hipError_t attn_merge(DType dt, const float* part_o, const float* part_ml,
                       const int32_t* tok_item_start, const int32_t* tok_rows, int n_tok, int n_q,
                       int n_kv, int head_dim, void* out, hipStream_t s);

@@ -51,6 +51,7 @@ int stream_fragments(int M, int N, int K, int splits, bool swiglu) {
   if (M > kStreamRows) return 0;
   const int groups = N / 64;
   if (2 * groups * splits <= kStreamBlocks) return 2;
+  if (swiglu && M <= 16 && groups <= 2 * kStreamBlocks) return 4;
   if (groups * splits > kStreamBlocks) return 0;
   return swiglu || K / splits <= kStreamMaxRange ? 4 : 0;
 }

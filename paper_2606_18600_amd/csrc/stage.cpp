@@ -43,6 +43,7 @@ stage_status fail(stage_status code, const char* fmt, ...) {
 constexpr int kRing = 4;             // pinned staging buffers in flight
 constexpr int kMaxSplits = 32;       // decode key splits per sequence, at most
 constexpr int kSplitMinBlocks = 4;   // at least 4 blocks (64 keys) per split
+constexpr int kSplitNoneBlocks = 8;  // a step with no more blocks than this per token: no splits
 constexpr int kSkinnyMaxRows = 128;  // decode-sized steps use split-K GEMMs
 constexpr int kMaxKvSplits = 4;      // K splits of the key/value columns of a prefill QKV
 constexpr int kMaxMidSplits = 8;     // K splits of the products of a small tiled step
@@ -339,10 +340,22 @@ bool build_meta(const stage* st, const stage_batch* pf, const stage_batch* dc, S
   // `attn_waves` waves (one round on the chip), at least kSplitMinBlocks
   // blocks each, at most kMaxSplits splits per sequence.
   long long units = 0;
-  for (int j = 0; j < nd; ++j) units += (dc->ctx_lens[j] + kBlock) / kBlock;
+  int longest = 0;
+  for (int j = 0; j < nd; ++j) {
+    const int nb = (dc->ctx_lens[j] + kBlock) / kBlock;
+    units += nb;
+    longest = std::max(longest, nb);
+  }
   units *= st->cfg.n_kv_heads;
   const int waves = decode_waves(st->attn_waves, nd, st->attn_scale);
-  const int bps_target = (int)std::max<long long>(kSplitMinBlocks, (units + waves - 1) / waves);
+  // Short contexts only: unsplit, which saves the merge of the splits (2.1 us
+  // and a launch per layer, against a chain of at most 4 more blocks).
+  const int bps_min = longest <= kSplitNoneBlocks ? kSplitNoneBlocks : kSplitMinBlocks;
+  const int bps_target = (int)std::max<long long>(bps_min, (units + waves - 1) / waves);
+  // The workspace holds kMaxSplits splits per sequence of a small stage; a
+  // step of few sequences on a larger one may use the others' room (three
+  // sequences of 20000-65000 keys: 32 splits each 82 us, 67 each 76).
+  const int max_splits = std::max<int>(kMaxSplits, (int)(st->max_ditems / std::max(1, nd)));
   for (int j = 0; j < nd; ++j) {
     const int ctx = dc->ctx_lens[j];
     const int g = np + j;
@@ -354,7 +367,7 @@ bool build_meta(const stage* st, const stage_batch* pf, const stage_batch* dc, S
     if (st->cfg.dtype != STAGE_BF16) continue;  // fp32 attention needs no split plan
     const int keys = ctx + 1;
     const int nb = (keys + kBlock - 1) / kBlock;
-    int splits = std::min(kMaxSplits, std::max(1, (nb + bps_target - 1) / bps_target));
+    int splits = std::min(max_splits, std::max(1, (nb + bps_target - 1) / bps_target));
     const int bps = (nb + splits - 1) / splits;
     splits = (nb + bps - 1) / bps;
     if ((size_t)(m.n_ditems + splits) > st->max_ditems) return false;
@@ -568,7 +581,8 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
   const int qw = nq * D, qkvw = (nq + 2 * nkv) * D;
   const int Tp = T - nd;
   SegTables tabs{pf && np ? pf->block_tables : nullptr, pf && np ? pf->max_blocks_per_seq : 0, np,
-                 dc && nd ? dc->block_tables : nullptr, dc && nd ? dc->max_blocks_per_seq : 0};
+                 dc && nd ? dc->block_tables : nullptr, dc && nd ? dc->max_blocks_per_seq : 0,
+                 st->ws + st->r_attn.off};
 
   float* x = st->at<float>(st->r_x);
   void* h = st->ws + st->r_h.off;
@@ -676,7 +690,7 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
             return attn_decode(dt, q, kvl, tabs, dm.ditems, dm.ditem_order, hm.n_ditems, nq,
                                st->at<float>(st->r_part_o), st->at<float>(st->r_part_ml), ls);
           });
-          L(STAGE_OP_ATTN, [&] {
+          if (hm.n_ditems > nd) L(STAGE_OP_ATTN, [&] {
             return attn_merge(dt, st->at<float>(st->r_part_o), st->at<float>(st->r_part_ml),
                               dm.item_start, dm.tok_rows, nd, nq, nkv, D, attn, ls);
           });
