@@ -430,6 +430,7 @@ void attn_prefill_bf16(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ kv, int n_kv, SegTables tabs,
     const PrefillItem* __restrict__ items, int n_q, bf16_t* __restrict__ out) {
   constexpr int BPS = kPfBPS;
+  static_assert(BPS * kBlock == kPrefillStage, "keys per stage");
   constexpr int NJ = D / 32;           // K fragments per block (and V fragments)
   constexpr int FR = 2 * NJ;           // fragments per block
   constexpr int SF = BPS * FR;         // fragments per stage
@@ -468,7 +469,14 @@ void attn_prefill_bf16(
   const size_t plane = (size_t)kBlock * D;
   const int kend = it.p0 + it.npos;  // keys [0, kend)
   const int nb = (kend + kBlock - 1) / kBlock;
-  const int nst = (nb + BPS - 1) / BPS;
+  // the stages [s0, nst) of this block (all of them unless the step is split)
+  int s0 = 0, nst = (nb + BPS - 1) / BPS;
+  const int parts = prefill_parts(tabs.parts.stages, it.p0, nst);
+  if ((int)blockIdx.z >= parts) return;
+  if (parts > 1) {
+    s0 = blockIdx.z * tabs.parts.stages;
+    if ((int)blockIdx.z + 1 < parts) nst = s0 + tabs.parts.stages;
+  }
 
   RowState st{-INFINITY, 0.f};
   f32x16_t oacc[NT];
@@ -608,16 +616,30 @@ void attn_prefill_bf16(
     __syncthreads();
   };
 
-  ids = fill_window(bt, 0, min(64, nb), lane);
-  issue(0, 0);
+  wbase = s0 * BPS;
+  ids = fill_window(bt, wbase, min(wbase + 64, nb), lane);
+  issue(s0, s0 & 1);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   const int nfull = min(nst, (it.p0 + 1) / (BPS * kBlock));
-  int stg = 0;
+  int stg = s0;
   for (; stg < nfull; ++stg) stage(std::false_type{}, stg);
   for (; stg < nst; ++stg) stage(std::true_type{}, stg);
 
   if (!rok) return;
+  if (parts > 1) {
+    // [d / 8][row][d % 8] of unnormalised output, then (max, sum) per row
+    float* po = tabs.parts.buf +
+                (((size_t)blockIdx.z * n_kv + kvh) * gridDim.x + lin / n_kv) * prefill_part_floats(D);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int qd = 0; qd < 4; ++qd)
+        *(f32x4_t*)(po + ((size_t)(t * 4 + qd) * kPrefillRows + r) * 8 + 4 * hi) =
+            f32x4_t{oacc[t][4 * qd], oacc[t][4 * qd + 1], oacc[t][4 * qd + 2], oacc[t][4 * qd + 3]};
+    if (hi == 0) *(float2*)(po + kPrefillRows * D + 2 * r) = make_float2(st.m, st.l);
+    return;
+  }
   const float inv = 1.0f / st.l;
   // packed activation layout (the O projection's input); 4 consecutive
   // columns share one 8-byte piece of a fragment lane
@@ -632,6 +654,56 @@ void attn_prefill_bf16(
       w[1] = pack_bf16x2(oacc[t][4 * qd + 2] * inv, oacc[t][4 * qd + 3] * inv);
       *(u32x2_t*)(out + packed_a_offset(row, col0 + 32 * t + 8 * qd, n_q * D)) = w;
     }
+}
+
+// Combine the parts of split prefill items: grid (item, kv head, 8-column
+// group); a thread takes 4 of the 8 columns of one row, in the layout the
+// parts were written in.
+template <int D>
+__global__ __launch_bounds__(2 * kPrefillRows) void attn_prefill_merge(
+    SegTables tabs, const PrefillItem* __restrict__ items, int n_q, bf16_t* __restrict__ out) {
+  const int n_items = gridDim.x, n_kv = gridDim.y, kvh = blockIdx.y;
+  const PrefillItem it = items[blockIdx.x];
+  const int nst = (it.p0 + it.npos + kPrefillStage - 1) / kPrefillStage;
+  const int parts = prefill_parts(tabs.parts.stages, it.p0, nst);
+  const int r = threadIdx.x >> 1, hi = threadIdx.x & 1;
+  const int G = n_q / n_kv, pi = r / G;
+  if (parts == 1 || pi >= it.npos) return;
+  const size_t step = (size_t)n_kv * n_items * prefill_part_floats(D);
+  const float* po = tabs.parts.buf + ((size_t)kvh * n_items + blockIdx.x) * prefill_part_floats(D);
+  const float* pm = po + kPrefillRows * D + 2 * r;
+  po += ((size_t)blockIdx.z * kPrefillRows + r) * 8 + 4 * hi;
+  float M = -INFINITY, L = 0.f;
+  f32x4_t o = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < parts; i += 4) {  // 4 parts' loads in flight
+    float2 ml[4];
+    f32x4_t v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const size_t off = (size_t)min(i + u, parts - 1) * step;
+      ml[u] = *(const float2*)(pm + off);
+      v[u] = *(const f32x4_t*)(po + off);
+    }
+    float cm = M;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) cm = fmaxf(cm, ml[u].x);
+    const float sc = exp2f(M - cm);
+    L *= sc;
+    o *= sc;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float w = i + u < parts ? exp2f(ml[u].x - cm) : 0.f;
+      L += w * ml[u].y;
+      o += w * v[u];
+    }
+    M = cm;
+  }
+  o *= 1.0f / L;
+  u32x2_t w;
+  w[0] = pack_bf16x2(o[0], o[1]);
+  w[1] = pack_bf16x2(o[2], o[3]);
+  *(u32x2_t*)(out + packed_a_offset(it.t0 + pi, (kvh * G + r % G) * D + 8 * blockIdx.z + 4 * hi,
+                                    n_q * D)) = w;
 }
 
 // fp32 mode, prefill and decode rows alike: one workgroup of kF32Waves waves
@@ -905,8 +977,12 @@ hipError_t attn_merge(DType dt, const float* part_o, const float* part_ml,
 template <int D>
 static void launch_prefill(dim3 grid, hipStream_t s, const void* q, KVLayer kv, SegTables tabs,
                            const PrefillItem* items, int n_q, void* out) {
+  grid.z = tabs.parts.most;
   attn_prefill_bf16<D><<<grid, kPfWaves * 64, 0, s>>>(
       (const bf16_t*)q, (const bf16_t*)kv.base, kv.n_kv, tabs, items, n_q, (bf16_t*)out);
+  if (grid.z == 1) return;
+  grid.z = D / 8;
+  attn_prefill_merge<D><<<grid, 2 * kPrefillRows, 0, s>>>(tabs, items, n_q, (bf16_t*)out);
 }
 
 hipError_t attn_prefill(DType dt, const void* q, KVLayer kv, SegTables tabs,

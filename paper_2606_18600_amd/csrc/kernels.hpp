@@ -31,6 +31,16 @@ struct RopeRows {
   float eps = 0.f;
 };
 
+// Key split of a step's prefill attention: an item's key stages (kPrefillStage
+// keys each) are shared by prefill_parts() blocks of `stages` stages, at most
+// `most` of them, whose results go to `buf` (prefill_part_floats() floats per
+// item, kv head and part) and are then combined. stages = 0: no split.
+struct PrefillParts {
+  float* buf = nullptr;
+  int32_t stages = 0;
+  int32_t most = 1;
+};
+
 // Block tables of the (at most) two segments of a step: sequences
 // [0, nseq0) read table 0, sequences [nseq0, ...) read table 1. attn_out
 // (bf16 mode): the packed attention output, where decode attention writes the
@@ -42,6 +52,7 @@ struct SegTables {
   const int32_t* bt1;
   int32_t stride1;
   void* attn_out = nullptr;
+  PrefillParts parts{};
 };
 
 // KV cache geometry of one layer: [num_blocks][n_kv][2][block * d]; plane 0
@@ -212,6 +223,21 @@ hipError_t attn_f32(const float* q, KVLayer kv, SegTables tabs, const int32_t* t
 // (position, head) rows of one prefill attention work item: 4 waves of one
 // 32-row tile.
 constexpr int kPrefillRows = 128;
+constexpr int kPrefillStage = 64;  // keys per stage
+// Parts of an item that starts at position p0 and has `nst` stages. Every row
+// of the item must see a key of every part, so no part starts after p0.
+constexpr int prefill_parts(int stages, int p0, int nst) {
+  if (stages <= 0) return 1;
+  const int a = (nst + stages - 1) / stages, b = p0 / (kPrefillStage * stages) + 1;
+  return a < b ? a : b;
+}
+constexpr size_t prefill_part_floats(int head_dim) {
+  return (size_t)kPrefillRows * (head_dim + 2);
+}
+// The split of n_items items with `total` stages in all, the longest of them
+// `longest`, into a buffer of `room` floats.
+PrefillParts prefill_split(int n_items, int n_kv, long long total, int longest, int head_dim,
+                           float* buf, size_t room);
 // Positions handled by one prefill work item for a GQA group size.
 int prefill_item_positions(DType dt, int group);
 

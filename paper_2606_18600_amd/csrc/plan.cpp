@@ -71,6 +71,26 @@ int stream_splits(int N, int K, int max_splits, bool swiglu) {
   return frags && (blocks * 10 >= kStreamBlocks * 7 || K <= 2048) ? s : 0;
 }
 
+PrefillParts prefill_split(int n_items, int n_kv, long long total, int longest, int head_dim,
+                           float* buf, size_t room) {
+  // Two blocks per CU (at the 70B shape: 154 rows behind 3535 keys 83 us on
+  // 80 blocks, 51 + 6 for the combining pass on 256, 38 + 8 on 512, 42 + 11
+  // on 768; 256 rows behind 30000 keys 600, 361 + 6, 283 + 9, 304 + 10; 512
+  // rows behind 8000 keys 202, 198, 161 + 10, 167 + 11), parts of at least 4
+  // stages, and only where the longest chain of stages (about 1.3 us each)
+  // gets shorter by more than the combining pass takes.
+  constexpr int kBlocks = 512, kMinStages = 4, kMinGain = 8;
+  const long long blocks = (long long)n_items * n_kv;
+  if (blocks >= kBlocks) return PrefillParts{};
+  long long stages = std::max<long long>(kMinStages, (total * n_kv + kBlocks - 1) / kBlocks);
+  for (; longest - stages >= kMinGain; stages *= 2) {
+    const long long most = (longest + stages - 1) / stages;
+    if ((size_t)(blocks * most) * prefill_part_floats(head_dim) <= room)
+      return PrefillParts{buf, (int32_t)stages, (int32_t)most};
+  }
+  return PrefillParts{};
+}
+
 int prefill_item_positions(DType dt, int group) {
   (void)dt;
   return kPrefillRows / group;

@@ -584,6 +584,20 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
                  dc && nd ? dc->block_tables : nullptr, dc && nd ? dc->max_blocks_per_seq : 0,
                  st->ws + st->r_attn.off};
 
+  if (dt == DT_BF16 && hm.n_pitems > 0) {
+    // the projections have been read when attention runs: their place holds
+    // the parts of a key split
+    long long total = 0;
+    int longest = 0;
+    for (int i = 0; i < hm.n_pitems; ++i) {
+      const int n = (hm.pitems[i].p0 + hm.pitems[i].npos + kPrefillStage - 1) / kPrefillStage;
+      total += n;
+      longest = std::max(longest, n);
+    }
+    tabs.parts = prefill_split(hm.n_pitems, nkv, total, longest, D, st->at<float>(st->r_qkv),
+                               st->r_qkv.bytes / 4);
+  }
+
   float* x = st->at<float>(st->r_x);
   void* h = st->ws + st->r_h.off;
   float* qkv = st->at<float>(st->r_qkv);
