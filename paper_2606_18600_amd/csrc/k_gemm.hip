@@ -205,14 +205,17 @@ __global__ __launch_bounds__(SK_WAVES * 64) void gemm_skinny_bf16(const bf16_t* 
   }
 }
 
-// The same product for 65..128 rows with 8 waves per block: wave w streams
+// The same product for 65 rows and more with 8 waves per block: wave w streams
 // weight group w % 4 and only k tile 2t + w / 4 of each 64-wide step (4 W
 // fragments), multiplying it with all MT m-tiles of A from the shared LDS
 // ring; the two waves of a group add their sums through LDS at the end and
 // each writes half of the m-tiles. A wave's MFMA work per step is then that
 // of the 4-wave kernel at 64 rows, and a block runs two waves per SIMD. With
 // 128 rows on 4 waves (one per SIMD) the MFMAs of a step took about as long
-// as the step's loads, so the two no longer overlapped.
+// as the step's loads, so the two no longer overlapped. Up to 192 rows it also
+// beats the tiled kernel where every weight is used by one row tile anyway
+// (launch_rows192): the weights go straight to registers instead of through
+// LDS, whose bandwidth 192-row tiles nearly exhaust.
 constexpr int SK8_WAVES = 8;
 
 template <int MT, int EPI>
@@ -222,9 +225,9 @@ void gemm_skinny8_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict__ 
   constexpr int NA = (2 * MT + SK8_WAVES - 1) / SK8_WAVES;  // A copies per wave and step
   constexpr int SLOT = SK8_WAVES * NA;                      // fragments per ring slot
   constexpr int WAIT = vmcnt_at_most(4 + NA);               // all but the newest step's loads
-  constexpr int H0 = MT < 4 ? MT : 4;                       // m-tiles [0, H0) end in k half 0
+  constexpr int H0 = (MT + 1) / 2;                          // m-tiles [0, H0) end in k half 0
   constexpr int RING = 3 * SLOT * 64;                       // u32x4 of the A ring
-  constexpr int RED = 4 * 4 * 4 * 64;                       // u32x4 of one reduction round
+  constexpr int RED = 4 * H0 * 4 * 64;                      // u32x4 of one reduction round
   __shared__ u32x4_t lds[RING > RED ? RING : RED];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int gw = wave & 3, kh = wave >> 2;
@@ -308,7 +311,7 @@ void gemm_skinny8_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict__ 
     for (int i = 0; i < H0; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        lds[((gw * 4 + i) * 4 + j) * 64 + lane] = __builtin_bit_cast(u32x4_t, acc[i][j]);
+        lds[((gw * H0 + i) * 4 + j) * 64 + lane] = __builtin_bit_cast(u32x4_t, acc[i][j]);
   }
   __syncthreads();
   if (kh == 0) {
@@ -316,7 +319,7 @@ void gemm_skinny8_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict__ 
     for (int i = 0; i < H0; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        acc[i][j] += __builtin_bit_cast(f32x4_t, lds[((gw * 4 + i) * 4 + j) * 64 + lane]);
+        acc[i][j] += __builtin_bit_cast(f32x4_t, lds[((gw * H0 + i) * 4 + j) * 64 + lane]);
   }
   if constexpr (MT > H0) {
     __syncthreads();
@@ -326,7 +329,7 @@ void gemm_skinny8_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict__ 
       for (int i = H0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          lds[((gw * 4 + i - H0) * 4 + j) * 64 + lane] = __builtin_bit_cast(u32x4_t, acc[i][j]);
+          lds[((gw * H0 + i - H0) * 4 + j) * 64 + lane] = __builtin_bit_cast(u32x4_t, acc[i][j]);
     }
     __syncthreads();
     if (kh == 1) {
@@ -334,7 +337,7 @@ void gemm_skinny8_bf16(const bf16_t* __restrict__ A, const bf16_t* __restrict__ 
       for (int i = H0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          acc[i][j] += __builtin_bit_cast(f32x4_t, lds[((gw * 4 + i - H0) * 4 + j) * 64 + lane]);
+          acc[i][j] += __builtin_bit_cast(f32x4_t, lds[((gw * H0 + i - H0) * 4 + j) * 64 + lane]);
     }
   }
   if (!live) return;
@@ -1305,10 +1308,34 @@ void launch_tiled(dim3 grid, hipStream_t s, const bf16_t* A, const bf16_t* W, in
         A, W, M, N, K, out, ldo, k_len, out_plane, rope);
 }
 
+// A product of 129..192 rows on gemm_skinny8_bf16: one row tile, weights read
+// once. At N = 57344, K = 8192 (SwiGLU) 144 rows take 159 us (187 on 192-row
+// tiles, 225 on 256-row ones), 176 rows 179 (196, 224), 191 rows 201 (191,
+// 224): 12 row tiles leave no registers to read ahead. Split over K, in 256
+// blocks: [8192, 28672] at 144 / 191 rows 88 / 103 us (102 / 107 and 124 /
+// 121), [8192, 8192] 32 / 37 (36 / 39 and 38 / 41).
+template <int EPI>
+hipError_t launch_rows192(const bf16_t* a, const bf16_t* w, int M, int N, int K, int kb_len,
+                          void* out, hipStream_t s) {
+  const dim3 grid((N / 64 + 3) / 4, (K + kb_len - 1) / kb_len);
+  const int threads = SK8_WAVES * 64;
+  switch ((M + 15) / 16) {
+    case 9: gemm_skinny8_bf16<9, EPI><<<grid, threads, 0, s>>>(a, w, M, N, K, kb_len, out); break;
+    case 10: gemm_skinny8_bf16<10, EPI><<<grid, threads, 0, s>>>(a, w, M, N, K, kb_len, out); break;
+    case 11: gemm_skinny8_bf16<11, EPI><<<grid, threads, 0, s>>>(a, w, M, N, K, kb_len, out); break;
+    case 12: gemm_skinny8_bf16<12, EPI><<<grid, threads, 0, s>>>(a, w, M, N, K, kb_len, out); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 hipError_t gemm_split_k(const void* A, const void* W, int M, int N, int K, int splits, float* out,
                         hipStream_t s) {
   if (M == 0) return hipSuccess;
   if (splits < 1 || N % 256 != 0 || K % (64 * splits) != 0) return hipErrorInvalidValue;
+  if (M > 128 && M <= 192)
+    return launch_rows192<SK_PARTIAL>((const bf16_t*)A, (const bf16_t*)W, M, N, K, K / splits, out,
+                                      s);
   dim3 grid((M + 255) / 256, N / 256, splits);
   launch_tiled<16, 4, 4, 2, EPI_STORE_F32>(grid, s, 
       (const bf16_t*)A, (const bf16_t*)W, M, N, K, out, N, K / splits, (size_t)M * N, RopeRows{});
@@ -1359,6 +1386,9 @@ hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int
     return hipErrorInvalidValue;
   }
   if (N % 128 != 0 || K % 64 != 0) return hipErrorInvalidValue;
+  // One row tile of at most 176 rows whose 256-column blocks occupy most CUs.
+  if (epi == EPI_SWIGLU && M > 128 && M <= 176 && N >= 160 * 256 && N <= 256 * 256)
+    return launch_rows192<SK_SWIGLU>((const bf16_t*)A, (const bf16_t*)W, M, N, K, K, out, s);
   // Three tilings: 256 x 256 and 192 x 256 (8 waves, one block per CU) and
   // 128 x 128 (4 waves, two per CU). A product costs about its number of
   // rounds of workgroups times the time of one round. Taking a round of 256

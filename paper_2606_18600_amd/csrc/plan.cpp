@@ -77,14 +77,19 @@ PrefillParts prefill_split(int n_items, int n_kv, long long total, int longest, 
   // 80 blocks, 51 + 6 for the combining pass on 256, 38 + 8 on 512, 42 + 11
   // on 768; 256 rows behind 30000 keys 600, 361 + 6, 283 + 9, 304 + 10; 512
   // rows behind 8000 keys 202, 198, 161 + 10, 167 + 11), parts of at least 4
-  // stages, and only where the longest chain of stages (about 1.3 us each)
-  // gets shorter by more than the combining pass takes.
-  constexpr int kBlocks = 512, kMinStages = 4, kMinGain = 8;
+  // stages, and only where that pays: a stage takes about 1.3 us with a block
+  // per CU and 2.4 with two, the combining pass 10 (400 rows behind 1000 keys
+  // gain nothing; 150 rows and one kv head behind 700, 10 stages' chain less
+  // on a nearly empty chip, 14 us per layer).
+  constexpr int kBlocks = 512, kMinStages = 4;
   const long long blocks = (long long)n_items * n_kv;
   if (blocks >= kBlocks) return PrefillParts{};
   long long stages = std::max<long long>(kMinStages, (total * n_kv + kBlocks - 1) / kBlocks);
-  for (; longest - stages >= kMinGain; stages *= 2) {
+  for (; longest > stages; stages *= 2) {
     const long long most = (longest + stages - 1) / stages;
+    const bool pays = blocks * most <= kBlocks / 2 ? longest - stages >= 8
+                                                   : 13LL * longest > 24 * stages + 100;
+    if (!pays) break;
     if ((size_t)(blocks * most) * prefill_part_floats(head_dim) <= room)
       return PrefillParts{buf, (int32_t)stages, (int32_t)most};
   }
