@@ -1337,6 +1337,13 @@ hipError_t gemm_split_k(const void* A, const void* W, int M, int N, int K, int s
     return launch_rows192<SK_PARTIAL>((const bf16_t*)A, (const bf16_t*)W, M, N, K, K / splits, out,
                                       s);
   dim3 grid((M + 255) / 256, N / 256, splits);
+  // 192-row tiles where they take no more blocks (257..384 rows: [8192, 28672]
+  // in 4 ranges 160 us at 384 rows against 197)
+  if ((M + 191) / 192 == (int)grid.x) {
+    launch_tiled<12, 4, 4, 2, EPI_STORE_F32>(grid, s, (const bf16_t*)A, (const bf16_t*)W, M, N, K,
+                                             out, N, K / splits, (size_t)M * N, RopeRows{});
+    return hipGetLastError();
+  }
   launch_tiled<16, 4, 4, 2, EPI_STORE_F32>(grid, s, 
       (const bf16_t*)A, (const bf16_t*)W, M, N, K, out, N, K / splits, (size_t)M * N, RopeRows{});
   return hipGetLastError();
@@ -1448,17 +1455,22 @@ hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int
     if (c192 < cost) best = T192, cost = c192;
     if (c256 <= cost) best = T256, cost = c256;
     const int m1 = M / 256 * 256;
-    // A SwiGLU product's rows past the last multiple of 256 (at most 128 of
+    // A SwiGLU product's rows past the last multiple of 256 (at most 176 of
     // them) on the split-K kernel with one K range and SwiGLU in its
     // epilogue: one more pass over the weights at ~6.3 TB/s, which costs
     // about N / 78000 rounds of 256 x 256 tiles (~5.3 TFLOP/s per CU). Taken
     // when that beats the tilings above, e.g. gate-up at 2048 + 128 rows:
     // -3% at N = 57344 (against the 128 x 128 tail below) and at N = 51200
     // (against 9 partly idle m-blocks), A/B on one box.
-    if (epi == EPI_SWIGLU && m1 > 0 && m1 < M && M - m1 <= 128 && swiglu_tail_skinny() &&
-        cost_of(T256, m1) + N / 78000.0 < cost) {
+    // 129..176 rows take an eighth longer.
+    const double tail = M - m1 <= 128 ? N / 78000.0 : N / 68000.0;
+    if (epi == EPI_SWIGLU && m1 > 0 && m1 < M && M - m1 <= 176 && swiglu_tail_skinny() &&
+        cost_of(T256, m1) + tail < cost) {
       const hipError_t e = launch(T256, 0, m1, 0, N);
       if (e != hipSuccess) return e;
+      if (M - m1 > 128)
+        return launch_rows192<SK_SWIGLU>(a + (size_t)(m1 / 16) * (K / 32) * 512, w, M - m1, N, K, K,
+                                         (bf16_t*)out + (size_t)(m1 / 16) * (N / 64) * 512, s);
       return gemm_skinny(a + (size_t)(m1 / 16) * (K / 32) * 512, W, M - m1, N, K, 1, true,
                          (bf16_t*)out + (size_t)(m1 / 16) * (N / 64) * 512, s);
     }

@@ -423,20 +423,45 @@ int qkv_kv_splits(const stage* st, int T) {
 
 // K splits for an [T, N] x [N, K]^T product of a bf16 tiled step (more rows
 // than the split-K decode GEMMs take), or 0. When its 256 x 256 tiles would
-// occupy less than half of the CUs for the whole K (e.g. O and down with 32
+// occupy at most half of the CUs for the whole K (e.g. O and down with 32
 // tiles per 256 rows), it runs over K ranges into fp32 partial planes that
 // the consumer sums (as in decode steps): as many ranges (a power of two, at
 // most 8) as keep the launch within one round and the planes within
-// kMidRows rows.
+// kMidRows rows. (Exactly half, 900 rows of the 70B shape: O and down 165 and
+// 515 us on one full round of 128 x 128 tiles, 110 and 344 in two ranges,
+// and about 10 more in each RMSNorm.)
 int mid_splits(const stage* st, int T, int N, int K) {
   if (st->cfg.dtype != STAGE_BF16 || T <= st->skinny_rows || N % 256 != 0) return 0;
   const int tiles = (T + 255) / 256 * (N / 256);
-  if (2 * tiles >= st->cus) return 0;
+  if (2 * tiles > st->cus) return 0;
   int best = 0;
   for (int sp = 2; sp <= kMaxMidSplits; sp *= 2)
     if (tiles * sp <= st->cus && K % (64 * sp) == 0 &&
         (size_t)sp * T * N <= mid_capacity(st->max_tokens, N))
       best = sp;
+  return best;
+}
+
+// K splits of the gate-up product of such a step, or 0. Its SwiGLU then needs
+// a pass over the planes, so the ranges are weighed: one range of K on 256-row
+// tiles takes about K / 55 us (192 rows and fewer: K / 64), the planes are
+// written and read at about 4 TB/s, the pass adds 3 us. The planes lie where
+// the QKV projection was. (A rank's share of the FFN: at 2 F = 7168, H = 8192
+// 150 rows took 88 us unsplit, 600 rows 113; at 14336, 400 rows 148.)
+int gate_up_splits(const stage* st, int T) {
+  const int N = 2 * st->cfg.ffn, K = st->cfg.hidden;
+  if (st->cfg.dtype != STAGE_BF16 || T <= st->skinny_rows || N % 256 != 0) return 0;
+  const long tiles = (long)(T + 255) / 256 * (N / 256);
+  const double range = T <= 192 ? K / 64.0 : K / 55.0;
+  int best = 0;
+  double cost = range;
+  for (int sp = 2; sp <= kMaxMidSplits; sp *= 2) {
+    if (tiles * sp > st->cus || K % (64 * sp) != 0 ||
+        (size_t)sp * T * N * 4 > st->r_qkv.bytes)
+      break;
+    const double c = range / sp + 2.0 * sp * T * N * 4 / 4e6 + 3;
+    if (c < cost) best = sp, cost = c;
+  }
   return best;
 }
 
@@ -628,7 +653,7 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
                        nq % 4 == 0 &&
                        st->q_rope_fused;
   const int mq = rt ? 0 : mid_splits(st, T, qkvw, H), mo = rt ? 0 : mid_splits(st, T, H, qw),
-            md = rt ? 0 : mid_splits(st, T, H, F);
+            md = rt ? 0 : mid_splits(st, T, H, F), mg = rt ? 0 : gate_up_splits(st, T);
   // the tail rows of the packed activations (whole 16-row fragments)
   auto tail_rows = [&](const void* act, int K) -> const void* {
     return (const uint16_t*)act + (size_t)(T0 / 16) * (K / 32) * 512;
@@ -744,7 +769,14 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
         L(STAGE_OP_DOWN, [&] { return gemm_skinny(m, w.w_down, T, H, F, sk_down, false, part_x, ls); });
         pending = Partials{part_x, sk_down};
       } else if (dt == DT_BF16) {
-        L(STAGE_OP_GATE_UP, [&] { return gemm(dt, EPI_SWIGLU, h, w.w_gate_up, T, 2 * F, H, m, ls); });
+        if (mg > 0) {
+          L(STAGE_OP_GATE_UP, [&] { return gemm_split_k(h, w.w_gate_up, T, 2 * F, H, mg, qkv, ls); });
+          L(STAGE_OP_NORM, [&] {
+            return swiglu_reduce_bf16(Partials{qkv, mg}, (uint16_t*)m, T, F, ls);
+          });
+        } else {
+          L(STAGE_OP_GATE_UP, [&] { return gemm(dt, EPI_SWIGLU, h, w.w_gate_up, T, 2 * F, H, m, ls); });
+        }
         if (md > 0) {
           L(STAGE_OP_DOWN, [&] { return gemm_split_k(m, w.w_down, T, H, F, md, part_x, ls); });
           pending = Partials{part_x, md};
