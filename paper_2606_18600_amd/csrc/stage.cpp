@@ -12,6 +12,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/stage.h"
@@ -277,9 +278,9 @@ void plan_workspace(stage* st) {
   const size_t max_items = st->max_ditems;
   take(st->r_part_o, max_items * qw * 4);
   take(st->r_part_ml, max_items * c.n_q_heads * 2 * 4);
-  // metadata: tok_seq, tok_pos [T]; decode items [max_items][4];
-  // item_start [max_seqs + 1]; tok_rows [max_seqs]; prefill items [T + max_seqs][4];
-  // decode item dispatch order [max_items]
+  // metadata, at most (build_meta): prefill items [T + max_seqs][4]; tok_seq,
+  // tok_pos [T]; tok_rows [max_seqs]; item_start [max_seqs + 1]; decode items
+  // [max_items][4] and their dispatch order [max_items]
   st->meta_ints = 2 * T + 4 * max_items + 2 * (size_t)st->max_seqs + 1 +
                   4 * (T + (size_t)st->max_seqs) + max_items;
   take(st->r_meta, st->meta_ints * 4);
@@ -295,31 +296,50 @@ struct StepMeta {
   int32_t* ditem_order;  // decode items in dispatch order (longest key range first)
   PrefillItem* pitems;
   int n_ditems = 0, n_pitems = 0;
+  size_t ints = 0;  // int32 values in all
 };
 
-// Lay out the metadata arrays over a base pointer (host staging or device).
-StepMeta meta_view(const stage* st, int32_t* base) {
-  const size_t T = st->max_tokens;
-  const size_t max_items = st->max_ditems;
-  StepMeta m;
-  m.tok_seq = base;
-  m.tok_pos = base + T;
-  m.ditems = reinterpret_cast<DecodeItem*>(base + 2 * T);
-  m.item_start = base + 2 * T + 4 * max_items;
-  m.tok_rows = m.item_start + st->max_seqs + 1;
-  m.pitems = reinterpret_cast<PrefillItem*>(m.tok_rows + st->max_seqs);
-  m.ditem_order = reinterpret_cast<int32_t*>(m.pitems + T + st->max_seqs);
+// The same arrays at another base (the device copy of the host staging).
+StepMeta rebase(StepMeta m, const int32_t* from, int32_t* to) {
+  auto move = [&](auto*& p) {
+    p = reinterpret_cast<std::decay_t<decltype(p)>>(to + (reinterpret_cast<int32_t*>(p) - from));
+  };
+  move(m.tok_seq);
+  move(m.tok_pos);
+  move(m.ditems);
+  move(m.item_start);
+  move(m.tok_rows);
+  move(m.ditem_order);
+  move(m.pitems);
   return m;
 }
 
-// Fill the step metadata. Returns false (having written nothing past the
-// item capacity) if the decode split plan would exceed max_ditems, which the
-// bound of max_decode_items rules out.
-bool build_meta(const stage* st, const stage_batch* pf, const stage_batch* dc, StepMeta& m) {
+// Fill the step metadata at `base` (room for meta_ints values), the arrays one
+// after another at the step's own sizes: an upload of at most 16 KB (any decode
+// step of a few hundred sequences) goes by a copy kernel, a larger one by the
+// DMA engine, whose hand-over costs about 15 us more per step. Returns false
+// (having written nothing past the item capacity) if the decode split plan
+// would exceed max_ditems, which the bound of max_decode_items rules out.
+bool build_meta(const stage* st, const stage_batch* pf, const stage_batch* dc, int T,
+                int32_t* base, StepMeta& m) {
   const int np = pf ? pf->num_seqs : 0, nd = dc ? dc->num_seqs : 0;
   int row = 0;
   const int ppw = prefill_item_positions((DType)st->cfg.dtype,
                                          st->cfg.n_q_heads / st->cfg.n_kv_heads);
+  int n_pitems = 0;
+  for (int s = 0; s < np; ++s) n_pitems += (pf->q_lens[s] + ppw - 1) / ppw;
+  size_t off = 0;
+  auto take = [&](size_t n) {
+    int32_t* p = base + off;
+    off += n;
+    return p;
+  };
+  m.pitems = reinterpret_cast<PrefillItem*>(take(4 * (size_t)n_pitems));
+  m.tok_seq = take(T);
+  m.tok_pos = take(T);
+  m.tok_rows = take(nd);
+  m.item_start = take((size_t)nd + 1);
+  m.ditems = reinterpret_cast<DecodeItem*>(take(0));  // as many as the plan makes, then their order
   m.n_pitems = 0;
   for (int s = 0; s < np; ++s) {
     const int q = pf->q_lens[s], ctx = pf->ctx_lens[s];
@@ -378,6 +398,9 @@ bool build_meta(const stage* st, const stage_batch* pf, const stage_batch* dc, S
     }
   }
   m.item_start[nd] = m.n_ditems;
+  take(4 * (size_t)m.n_ditems);
+  m.ditem_order = take(m.n_ditems);
+  m.ints = off;
   // Dispatch the longest key ranges first (the splits of one sequence
   // differ by at most one block, those of different sequences by up to 2x),
   // so that the short ones fill the tail of the launch.
@@ -596,11 +619,11 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
   // metadata: host build in a pinned staging slot, one async upload
   int slot = 0;
   if ((vs = take_slot(st, &slot)) != STAGE_OK) return vs;
-  StepMeta hm = meta_view(st, st->staging[slot]);
-  if (!build_meta(st, pf, dc, hm))
+  StepMeta hm;
+  if (!build_meta(st, pf, dc, T, st->staging[slot], hm))
     return fail(STAGE_ERR_CAPACITY, "decode split plan exceeds %zu items", st->max_ditems);
-  if ((vs = upload_slot(st, slot, st->meta_ints, s)) != STAGE_OK) return vs;
-  StepMeta dm = meta_view(st, st->at<int32_t>(st->r_meta));
+  if ((vs = upload_slot(st, slot, hm.ints, s)) != STAGE_OK) return vs;
+  const StepMeta dm = rebase(hm, st->staging[slot], st->at<int32_t>(st->r_meta));
 
   const int H = c.hidden, D = c.head_dim, nq = c.n_q_heads, nkv = c.n_kv_heads, F = c.ffn;
   const int qw = nq * D, qkvw = (nq + 2 * nkv) * D;
