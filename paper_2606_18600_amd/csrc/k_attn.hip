@@ -387,8 +387,13 @@ __global__ __launch_bounds__(WPT == 1 ? 256 : WPT * 64) void attn_merge_kernel(
 // head kvh*G + r % G; wave w owns rows 32w .. 32w + 31 as one 32-row tile of
 // v_mfma_f32_32x32x16_bf16 (lane l: row l % 32). Keys run in stages of BPS
 // 16-token blocks: each stage's K and V fragments are copied once into LDS
-// (direct loads, two buffers) and read by all waves, so a key is fetched
-// once per workgroup instead of once per 32 rows. Scores of a whole stage
+// (direct loads, two buffers each; K two stages ahead, V one) and read by all
+// waves, so a key is fetched once per workgroup instead of once per 32 rows.
+// The score products of a stage run between the exponentials of the stage
+// before it, in program order, so that a wave overlaps its own matrix and
+// vector work and the LDS reads of K hide behind both (one stage at a time,
+// the two waves of a SIMD mostly alternated: 2048 rows behind 61440 keys 4217
+// us with MFMA busy 54%, now 4050). Scores of a whole stage
 // are reduced together; the running maximum is only moved (and the
 // accumulators rescaled) when it grows by more than 2^8, so P stays below
 // 256 and the rescale is rare after the first stage.
@@ -432,15 +437,14 @@ void attn_prefill_bf16(
   constexpr int BPS = kPfBPS;
   static_assert(BPS * kBlock == kPrefillStage, "keys per stage");
   constexpr int NJ = D / 32;           // K fragments per block (and V fragments)
-  constexpr int FR = 2 * NJ;           // fragments per block
-  constexpr int SF = BPS * FR;         // fragments per stage
-  constexpr int PER = SF / kPfWaves;   // fragment copies per wave and stage
+  constexpr int KF = BPS * NJ;         // K fragments per stage (and V fragments)
+  constexpr int PER = KF / kPfWaves;   // K copies per wave and stage (and V copies)
   constexpr int NP = BPS / 2;          // 32-key tiles per stage
   constexpr int ND = D / 16;           // 16-wide d slices (score products per tile)
   constexpr int NT = D / 32;           // 32-wide d tiles of O^T
-  static_assert(SF % kPfWaves == 0, "stage split");
+  static_assert(KF % kPfWaves == 0, "stage split");
   static_assert(BPS % 2 == 0, "score tiles take key blocks in pairs");
-  __shared__ u32x4_t lds[2][SF * 64];
+  __shared__ u32x4_t lds[4][KF * 64];  // K of even and odd stages, then V
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, hi = lane >> 5;
   // Workgroup b runs on XCD b % 8, each XCD with its own L2. Take the kv head
@@ -486,18 +490,25 @@ void attn_prefill_bf16(
     for (int v = 0; v < 16; ++v) oacc[t][v] = 0.f;
 
   // Block ids, 64 at a time (a multiple of BPS, so a stage never straddles
-  // two windows).
+  // two windows). `window` before the copies of a stage that may open a new one.
   int wbase = 0, ids = 0;
-  auto issue = [&](int stg, int buf) {
+  auto window = [&](int stg) {
+    if (stg * BPS - wbase >= 64) {
+      wbase = stg * BPS;
+      ids = fill_window(bt, wbase, min(wbase + 64, nb), lane);
+    }
+  };
+  // copies of a stage's K (plane 0) or V (plane 1) fragments into LDS
+  auto issue = [&](int stg, int vp) {
+    const int buf = 2 * vp + (stg & 1);
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       const int f = wave * PER + p;
-      const int c = f % FR;
-      int b = stg * BPS + f / FR;
+      int b = stg * BPS + f / NJ;
       b = b < nb ? b : nb - 1;  // past the end: a valid block, never used
       const bf16_t* src = kv + ((size_t)__builtin_amdgcn_readlane(ids, b - wbase) * n_kv + kvh) *
                                    (2 * plane) +
-                          (c < NJ ? c * 512 : plane + (c - NJ) * 512) + lane * 8;
+                          vp * plane + (f % NJ) * 512 + lane * 8;
       __builtin_amdgcn_global_load_lds((const void*)src, (lds_ptr_t)&lds[buf][f * 64], 16, 0, 0);
     }
   };
@@ -509,33 +520,33 @@ void attn_prefill_bf16(
   const int kslot = (lane & 15) + 16 * hi;
   const int vslot = (lane & 15) + 16 * hi, vhalf = (lane >> 4) & 1;
 
-  // One stage of BPS key blocks. Stages whose last key is at or before the
-  // first query position of the item need no causal mask (for a long
-  // context, nearly all of them).
-  auto stage = [&](auto masked, int stg) {
-    constexpr bool kMask = decltype(masked)::value;
-    const int buf = stg & 1;
-    if (stg + 1 < nst) {
-      if ((stg + 1) * BPS - wbase >= 64) {
-        wbase = (stg + 1) * BPS;
-        ids = fill_window(bt, wbase, min(wbase + 64, nb), lane);
-      }
-      issue(stg + 1, buf ^ 1);
+  // operand and product number i of a stage's raw scores (one 32-key tile per
+  // pair of blocks)
+  auto kload = [&](const u32x4_t* L, int i) {
+    const int sl = i / NP, t = i % NP;
+    return L[((2 * t + kblk) * NJ + sl / 2) * 64 + kslot + 32 * (sl % 2)];
+  };
+  auto score = [&](f32x16_t (&sc)[NP], u32x4_t kf, int i) {
+    if (i < NP) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sc[i][v] = 0.f;
     }
-    const u32x4_t* L = lds[buf];
-    // raw scores of the stage, one 32-key tile per pair of blocks
-    f32x16_t sc[NP];
-#pragma unroll
-    for (int t = 0; t < NP; ++t)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) sc[t][v] = 0.f;
-#pragma unroll
-    for (int s = 0; s < ND; ++s)
-#pragma unroll
-      for (int t = 0; t < NP; ++t) {
-        const u32x4_t kf = L[((2 * t + kblk) * FR + s / 2) * 64 + kslot + 32 * (s % 2)];
-        sc[t] = mfma32x32x16(kf, qf[s], sc[t]);
+    sc[i % NP] = mfma32x32x16(kf, qf[i / NP], sc[i % NP]);
+  };
+
+  // One stage of BPS key blocks, whose raw scores are in sc. The scores of the
+  // next stage (`more`) go to sn, their products between this stage's
+  // exponentials. Stages whose last key is at or before the first query
+  // position of the item need no causal mask (for a long context, nearly all).
+  auto stage = [&](auto masked, auto more, int stg, f32x16_t (&sc)[NP], f32x16_t (&sn)[NP]) {
+    constexpr bool kMask = decltype(masked)::value, kMore = decltype(more)::value;
+    if constexpr (kMore) {
+      issue(stg + 1, 1);
+      if (stg + 2 < nst) {
+        window(stg + 2);
+        issue(stg + 2, 0);
       }
+    }
     if constexpr (kMask) {
 #pragma unroll
       for (int t = 0; t < NP; ++t)
@@ -559,19 +570,35 @@ void attn_prefill_bf16(
 #pragma unroll
       for (int t = 0; t < NT; ++t) oacc[t] *= alpha;
     }
+    // P and, product by product between its arithmetic, the next stage's
+    // scores: one product, the read of the operand KD products further on,
+    // and EP exponentials, in this order (the scheduling barriers keep it).
+    constexpr int MF = ND * NP, KD = 4, EP = NP * 16 / MF;
+    const u32x4_t* LK = lds[(stg + 1) & 1];
+    u32x4_t kf[MF];
+    if constexpr (kMore) {
+#pragma unroll
+      for (int i = 0; i < KD; ++i) kf[i] = kload(LK, i);
+    }
     u32x4_t pb[NP][2];
     float ps = 0.f;
 #pragma unroll
-    for (int t = 0; t < NP; ++t)
-#pragma unroll
-      for (int z = 0; z < 2; ++z) {
-        float p[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p[e] = fast_exp2(fmaf(sc[t][8 * z + e], scale, -mn));
-        ps += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-        pb[t][z] = u32x4_t{pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]),
-                           pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7])};
+    for (int i = 0; i < MF; ++i) {
+      if constexpr (kMore) {
+        __builtin_amdgcn_sched_barrier(0);
+        score(sn, kf[i], i);
+        if (i + KD < MF) kf[i + KD] = kload(LK, i + KD);
       }
+#pragma unroll
+      for (int e = 0; e < EP; e += 2) {
+        const int v = i * EP + e, t = v / 16, u = v % 16;
+        const float p0 = fast_exp2(fmaf(sc[t][u], scale, -mn));
+        const float p1 = fast_exp2(fmaf(sc[t][u + 1], scale, -mn));
+        ps += p0 + p1;
+        pb[t][u / 8][u % 8 / 2] = pack_bf16x2(p0, p1);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
     st.l = st.l * alpha + row2_sum(ps);
     st.m = mn;
     // O^T += V^T P^T, block by block. The two 8-byte pieces of each V^T
@@ -579,9 +606,9 @@ void attn_prefill_bf16(
     // reads, so that the compiler does not merge them with neighbouring
     // pieces and then assemble the operands with register moves).
     typedef const volatile u32x2_t __attribute__((address_space(3)))* lds_u32x2_ptr;
-    const lds_u32x2_ptr L2 = (lds_u32x2_ptr)L;
+    const lds_u32x2_ptr L2 = (lds_u32x2_ptr)lds[2 + (stg & 1)];
     auto vload = [&](int blk, int t) {
-      const int f = blk * FR + NJ + t;
+      const int f = blk * NJ + t;
       const u32x2_t a0 = L2[(f * 64 + vslot) * 2 + vhalf];
       const u32x2_t a1 = L2[(f * 64 + vslot + 32) * 2 + vhalf];
       return u32x4_t{a0[0], a0[1], a1[0], a1[1]};
@@ -612,19 +639,36 @@ void attn_prefill_bf16(
       if (g + PD < NG) __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);  // 4 LDS reads
       __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                    // then the MFMAs
     }
-    __builtin_amdgcn_s_waitcnt(0);  // the next stage has landed in LDS
+    __builtin_amdgcn_s_waitcnt(0);  // the copies have landed in LDS
     __syncthreads();
   };
 
   wbase = s0 * BPS;
   ids = fill_window(bt, wbase, min(wbase + 64, nb), lane);
-  issue(s0, s0 & 1);
+  issue(s0, 0);
+  issue(s0, 1);
+  if (s0 + 1 < nst) issue(s0 + 1, 0);  // (a stage is never a window's last)
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
+  f32x16_t sa[NP], sb[NP];
+#pragma unroll
+  for (int i = 0; i < ND * NP; ++i) score(sa, kload(lds[s0 & 1], i), i);
+  __syncthreads();  // every wave has read the first K
   const int nfull = min(nst, (it.p0 + 1) / (BPS * kBlock));
+  // stages in pairs, their scores alternating between sa and sb
+  const std::true_type yes{};
+  const std::false_type no{};
   int stg = s0;
-  for (; stg < nfull; ++stg) stage(std::false_type{}, stg);
-  for (; stg < nst; ++stg) stage(std::true_type{}, stg);
+  for (; stg + 1 < min(nfull, nst - 1); stg += 2) {
+    stage(no, yes, stg, sa, sb);
+    stage(no, yes, stg + 1, sb, sa);
+  }
+  for (; stg + 1 < nst; ++stg) {
+    stage(yes, yes, stg, sa, sb);
+#pragma unroll
+    for (int t = 0; t < NP; ++t) sa[t] = sb[t];
+  }
+  stage(yes, no, stg, sa, sb);
 
   if (!rok) return;
   if (parts > 1) {
