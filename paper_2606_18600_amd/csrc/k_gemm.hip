@@ -961,58 +961,76 @@ __global__ __launch_bounds__(WM * WN * 64, 512 / (WM * WN * 64)) void gemm_tiled
 // ---------------------------------------------------------------------------
 // fp32 GEMM (fp32 mode, row-major operands)
 // ---------------------------------------------------------------------------
-// fp32 operands and accumulators on v_mfma_f32_32x32x2_f32 (every product and
-// sum in 32 bits). A wave owns RT x CT tiles of 32 x 32; WM x WN such waves
-// cover the block tile and KS groups of them take a K range each, added
-// through LDS in range order. Bound: the fp32 matrix rate is a sixteenth of
-// the bf16 one, so an operand byte feeds its product slowly enough to come
-// straight from L1/L2 (16 B per clock and CU at 2 x 2 tiles per wave); LDS
-// staging would add a barrier per step and save nothing. What the fp32 mode's
-// sizes (a few hundred rows) lack is blocks, hence small tiles and K ranges
-// within a block. A lane loads 4 consecutive k of its row at a time (lane l:
-// row l % 32, k 8 v + 4 (l / 32) .. + 3), and step (v, e) multiplies k 8 v + e
-// and 8 v + 4 + e, the same permutation of k for both operands. Rows and columns past the end repeat
-// the last one and are not stored. Measured against SIMT tiles of 64 or 32
-// columns with LDS staging: 454 x 1280 x 512 91 -> 16.5 us, 454 x 512 x 1024
-// 63 -> 14 us, 151 x 256 x 704 58 -> 11 us. (KC = 64 on the small tiles, all
-// of a wave's K in flight at once, was slower: 16.5 -> 22.8 us.)
+// fp32 operands and accumulators on v_mfma_f32_32x32x2_f32 or 16x16x4_f32
+// (every product and sum in 32 bits). A wave owns RT x CT tiles of S x S; WM x
+// WN such waves cover the block tile and KS groups of them take a K range
+// each, added through LDS in range order. Bound: the fp32 matrix rate is a
+// sixteenth of the bf16 one, so an operand byte feeds its product slowly
+// enough to come straight from L1/L2 (16 B per clock and CU at 2 x 2 tiles of
+// 32 per wave); LDS staging would add a barrier per step and save nothing.
+// What the fp32 mode's sizes (a few hundred rows) lack is blocks, hence small
+// tiles and K ranges within a block. A lane loads 4 consecutive k of its row at
+// a time (lane l: row l % S, k group l / S), and step (v, e) multiplies element
+// e of every group's v-th load, the same permutation of k for both operands.
+// Rows and columns past the end repeat the last one and are not stored.
+// Measured against SIMT tiles of 64 or 32 columns with LDS staging: 438 x 1280
+// x 512 91 -> 14.7 us, 438 x 512 x 1024 63 -> 11 us, 151 x 256 x 704 58 -> 4.2
+// us (7.4 on 32 x 32 tiles). Longer chunks per load round (KC 32, 64) and more
+// K ranges (8, 16) are 5-25% slower at 438 rows.
 //
-// EPI_SWIGLU: N = 2 F, gate rows then up rows; CT = 2, tile 0 holds 32 gate
+// EPI_SWIGLU: N = 2 F, gate rows then up rows; CT = 2, tile 0 holds S gate
 // columns and tile 1 the matching up columns, and out is [M, F].
+template <int S> struct f32_tile;
+template <> struct f32_tile<32> {
+  typedef f32x16_t acc;
+  static constexpr int kVals = 16;
+  // row of value v of the C tile in k group g (lane l: column l % S)
+  __device__ static __forceinline__ int row(int v, int g) { return 8 * (v >> 2) + 4 * g + (v & 3); }
+  __device__ static __forceinline__ acc mul(float a, float b, acc c) { return mfma32x32x2(a, b, c); }
+};
+template <> struct f32_tile<16> {
+  typedef f32x4_t acc;
+  static constexpr int kVals = 4;
+  __device__ static __forceinline__ int row(int v, int g) { return 4 * g + v; }
+  __device__ static __forceinline__ acc mul(float a, float b, acc c) { return mfma16x16x4(a, b, c); }
+};
+
 // the caller's fp32 weights may lie at any multiple of 4 bytes
 typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
 
-template <int RT, int CT, int WM, int WN, int KS, int KC, int EPI>
+template <int S, int RT, int CT, int WM, int WN, int KS, int KC, int EPI>
 __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_f32(const float* __restrict__ A,
                                                               const float* __restrict__ W, int M,
                                                               int N, int K,
                                                               float* __restrict__ out) {
-  constexpr int NV = KC / 8;  // float4 per lane, row tile and chunk
+  using Tile = f32_tile<S>;
+  using acc_t = typename Tile::acc;
+  constexpr int KL = 4 * (64 / S);  // k per load of all groups
+  constexpr int NV = KC / KL;       // loads per lane, tile and chunk
   constexpr bool kSwiglu = EPI == EPI_SWIGLU;
-  static_assert(!kSwiglu || CT == 2, "a gate and an up tile");
-  __shared__ f32x16_t red[KS > 1 ? (KS - 1) * WM * WN * RT * CT * 64 : 1];
+  static_assert(KC % KL == 0 && (!kSwiglu || CT == 2), "whole loads; a gate and an up tile");
+  __shared__ acc_t red[KS > 1 ? (KS - 1) * WM * WN * RT * CT * 64 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l32 = lane & 31, hi = lane >> 5;
+  const int lr = lane % S, lg = lane / S;
   const int ks = wave / (WM * WN), wt = wave % (WM * WN);
-  const int m0 = (blockIdx.x * WM + wt / WN) * RT * 32;
-  const int n0 = (blockIdx.y * WN + wt % WN) * (kSwiglu ? 1 : CT) * 32;
+  const int m0 = (blockIdx.x * WM + wt / WN) * RT * S;
+  const int n0 = (blockIdx.y * WN + wt % WN) * (kSwiglu ? 1 : CT) * S;
   const float* ap[RT];
   const float* wp[CT];
 #pragma unroll
-  for (int i = 0; i < RT; ++i)
-    ap[i] = A + (size_t)min(m0 + 32 * i + l32, M - 1) * K + hi * 4;
+  for (int i = 0; i < RT; ++i) ap[i] = A + (size_t)min(m0 + S * i + lr, M - 1) * K + lg * 4;
 #pragma unroll
   for (int j = 0; j < CT; ++j) {
-    const int n = kSwiglu ? min(n0 + l32, N / 2 - 1) + j * (N / 2) : min(n0 + 32 * j + l32, N - 1);
-    wp[j] = W + (size_t)n * K + hi * 4;
+    const int n = kSwiglu ? min(n0 + lr, N / 2 - 1) + j * (N / 2) : min(n0 + S * j + lr, N - 1);
+    wp[j] = W + (size_t)n * K + lg * 4;
   }
-  f32x16_t acc[RT][CT];
+  acc_t acc[RT][CT];
 #pragma unroll
   for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int j = 0; j < CT; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < Tile::kVals; ++v) acc[i][j][v] = 0.f;
 
   // this wave's chunks of KC (K % KC == 0)
   const int chunks = K / KC, c0 = chunks * ks / KS, c1 = chunks * (ks + 1) / KS;
@@ -1022,9 +1040,9 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_f32(const float* __res
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
 #pragma unroll
-      for (int i = 0; i < RT; ++i) a[i][v] = *(const f32x4_t*)(ap[i] + (size_t)c * KC + 8 * v);
+      for (int i = 0; i < RT; ++i) a[i][v] = *(const f32x4_t*)(ap[i] + (size_t)c * KC + KL * v);
 #pragma unroll
-      for (int j = 0; j < CT; ++j) w[j][v] = *(const f32x4_any_t*)(wp[j] + (size_t)c * KC + 8 * v);
+      for (int j = 0; j < CT; ++j) w[j][v] = *(const f32x4_any_t*)(wp[j] + (size_t)c * KC + KL * v);
     }
   };
   auto compute = [&](const f32x4_t (&a)[RT][NV], const f32x4_t (&w)[CT][NV]) {
@@ -1036,7 +1054,7 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_f32(const float* __res
         for (int i = 0; i < RT; ++i)
 #pragma unroll
           for (int j = 0; j < CT; ++j)
-            acc[i][j] = mfma32x32x2(a[i][v][e], w[j][v][e], acc[i][j]);
+            acc[i][j] = Tile::mul(a[i][v][e], w[j][v][e], acc[i][j]);
   };
   if (c0 < c1) {
     load(ax, wx, c0);
@@ -1068,20 +1086,19 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_f32(const float* __res
           acc[i][j] += red[(((q * WM * WN + wt) * RT + i) * CT + j) * 64 + lane];
   }
 
-  // C layout: lane l holds column l % 32, value v row 8 (v / 4) + 4 (l / 32) + v % 4
 #pragma unroll
   for (int i = 0; i < RT; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int m = m0 + 32 * i + 8 * (v >> 2) + 4 * hi + (v & 3);
+    for (int v = 0; v < Tile::kVals; ++v) {
+      const int m = m0 + S * i + Tile::row(v, lg);
       if (m >= M) continue;
       if constexpr (kSwiglu) {
-        const int n = n0 + l32;
+        const int n = n0 + lr;
         if (n < N / 2) out[(size_t)m * (N / 2) + n] = silu_f(acc[i][0][v]) * acc[i][1][v];
       } else {
 #pragma unroll
         for (int j = 0; j < CT; ++j) {
-          const int n = n0 + 32 * j + l32;
+          const int n = n0 + S * j + lr;
           if (n >= N) continue;
           float* o = out + (size_t)m * N + n;
           if (EPI == EPI_RESID_ADD)
@@ -1093,9 +1110,11 @@ __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_f32(const float* __res
     }
 }
 
-// The largest tile that still gives every CU a block; below that 32 x 32
-// tiles with 4 or, where even those are few and K is long, 8 K ranges per
-// block. (SwiGLU: a 32-column tile is a gate and an up tile.)
+// The largest tile that still gives every CU a block; below that 32 x 32 tiles
+// with 4 K ranges per block, and where even those occupy at most half of the
+// CUs 16 x 16 ones (151 rows, N = 256: K = 256 4.2 -> 2.7 us, K = 704 7.4 ->
+// 4.2; 438 rows, N = 512, 224 tiles of 32: 11 -> 17). (SwiGLU: a tile of
+// columns is a gate and an up tile.)
 template <int EPI>
 hipError_t launch_gemm_f32(const float* A, const float* W, int M, int N, int K, float* out,
                            hipStream_t s) {
@@ -1106,13 +1125,13 @@ hipError_t launch_gemm_f32(const float* A, const float* W, int M, int N, int K, 
   auto tiles = [&](int tm, int tn) { return (long)up(M, tm) * up(cols, tn); };
   constexpr int BN = kSwiglu ? 64 : 128;  // columns of the largest tile
   if (tiles(128, BN) >= 256)
-    gemm_f32<2, 2, 2, 2, 1, 16, EPI><<<dim3(up(M, 128), up(cols, BN)), 256, 0, s>>>(A, W, M, N, K, out);
+    gemm_f32<32, 2, 2, 2, 2, 1, 16, EPI><<<dim3(up(M, 128), up(cols, BN)), 256, 0, s>>>(A, W, M, N, K, out);
   else if (tiles(64, 64) >= 256)
-    gemm_f32<1, CT, 2, 2, 2, 32, EPI><<<dim3(up(M, 64), up(cols, 64)), 512, 0, s>>>(A, W, M, N, K, out);
-  else if (tiles(32, 32) > 512 || K < 512)
-    gemm_f32<1, CT, 1, 1, 4, 32, EPI><<<dim3(up(M, 32), up(cols, 32)), 256, 0, s>>>(A, W, M, N, K, out);
+    gemm_f32<32, 1, CT, 2, 2, 2, 32, EPI><<<dim3(up(M, 64), up(cols, 64)), 512, 0, s>>>(A, W, M, N, K, out);
+  else if (tiles(32, 32) > 128)
+    gemm_f32<32, 1, CT, 1, 1, 4, 16, EPI><<<dim3(up(M, 32), up(cols, 32)), 256, 0, s>>>(A, W, M, N, K, out);
   else
-    gemm_f32<1, CT, 1, 1, 8, 32, EPI><<<dim3(up(M, 32), up(cols, 32)), 512, 0, s>>>(A, W, M, N, K, out);
+    gemm_f32<16, 1, CT, 1, 1, 4, 16, EPI><<<dim3(up(M, 16), up(cols, 16)), 256, 0, s>>>(A, W, M, N, K, out);
   return hipGetLastError();
 }
 

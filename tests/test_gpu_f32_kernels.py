@@ -1,6 +1,5 @@
 """The fp32 mode's matrix-core kernels at the sizes where their dispatch
-turns: GEMM tiles of 128, 64 and 32 with 4 or 8 K ranges per block (through
-the LM head, whose vocabulary and row count are free in the fp32 mode), and
+turns: GEMM tiles of 128, 64, 32 and 16 (through the LM head, whose vocabulary and row count are free in the fp32 mode), and
 attention blocks that hold tokens of several sequences."""
 
 from __future__ import annotations
@@ -33,7 +32,7 @@ def _stage(shape, seed, blocks=128, max_tokens=512, max_seqs=24, fill=0.0):
 @pytest.mark.parametrize("hidden", [256, 640])
 @pytest.mark.parametrize("rows,vocab", [(8, 131), (9, 1), (9, 131), (31, 33), (32, 32), (33, 65),
                                         (64, 4096), (65, 4129), (129, 16384), (256, 16500),
-                                        (300, 515)])
+                                        (300, 515), (128, 1024), (128, 1025), (17, 15)])
 def test_lm_head_tiles(hidden, rows, vocab):
     """logits against float64 on the same stored values. A dot product of
     K <= 640 terms in fp32, in any order, is within K * 2^-24 of the sum of
