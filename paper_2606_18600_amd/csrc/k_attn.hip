@@ -155,23 +155,16 @@ __device__ __forceinline__ void softmax_pv(f32x4_t s, RowState& st, f32x4_t* oac
   }
 }
 
+// One wave over the 16-key blocks [b0, b1) of an item's keys for one kv head:
+// unnormalised output and softmax state of the group's rows (none: st.m =
+// -inf, zeros).
 template <int D>
-__global__ __launch_bounds__(256) void attn_decode_bf16(const bf16_t* __restrict__ q,
-                                                        const bf16_t* __restrict__ kv, int n_kv,
-                                                        SegTables tabs,
-                                                        const DecodeItem* __restrict__ items,
-                                                        const int32_t* __restrict__ order,
-                                                        int n_items, int n_q,
-                                                        float* __restrict__ part_o,
-                                                        float* __restrict__ part_ml) {
+__device__ __forceinline__ void decode_blocks(const bf16_t* __restrict__ q,
+                                              const bf16_t* __restrict__ kv, int n_kv,
+                                              const SegTables& tabs, const DecodeItem& it, int kvh,
+                                              int n_q, int b0, int b1, RowState& st,
+                                              f32x4_t (&oacc)[D / 16]) {
   const int lane = threadIdx.x & 63;
-  const int kvh = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (kvh >= n_kv) return;
-  const int idx = order[blockIdx.x];
-  const DecodeItem it = items[idx];
-  // items of one token are adjacent, from key 0 on: alone if the next item
-  // starts at key 0 again
-  const bool alone = it.k0 == 0 && (idx + 1 == n_items || items[idx + 1].k0 == 0);
   const int G = n_q / n_kv;
   const int row = lane & 15;  // query head within the group
   const bool row_ok = row < G;
@@ -190,12 +183,10 @@ __global__ __launch_bounds__(256) void attn_decode_bf16(const bf16_t* __restrict
   const int32_t* bt = seq_table(tabs, it.seq);
   const size_t plane = (size_t)kBlock * D;
   const size_t head_stride = 2 * plane;
-  RowState st{-INFINITY, 0.f};
-  f32x4_t oacc[D / 16];
+  st = RowState{-INFINITY, 0.f};
 #pragma unroll
   for (int t = 0; t < D / 16; ++t) oacc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int b0 = it.k0 / kBlock, b1 = (it.k1 + kBlock - 1) / kBlock;
   // Two register sets in ping-pong (no copies between them), so a block's
   // loads stay in flight while the previous block is processed; the
   // prefetch index is clamped to the window's last block and its data is
@@ -239,8 +230,31 @@ __global__ __launch_bounds__(256) void attn_decode_bf16(const bf16_t* __restrict
     }
     if (b < we) step(kx, vx, b);
   }
+}
 
-  if (!row_ok) return;
+template <int D>
+__global__ __launch_bounds__(256) void attn_decode_bf16(const bf16_t* __restrict__ q,
+                                                        const bf16_t* __restrict__ kv, int n_kv,
+                                                        SegTables tabs,
+                                                        const DecodeItem* __restrict__ items,
+                                                        const int32_t* __restrict__ order,
+                                                        int n_items, int n_q,
+                                                        float* __restrict__ part_o,
+                                                        float* __restrict__ part_ml) {
+  const int lane = threadIdx.x & 63;
+  const int kvh = blockIdx.y * 4 + (threadIdx.x >> 6);
+  if (kvh >= n_kv) return;
+  const int idx = order[blockIdx.x];
+  const DecodeItem it = items[idx];
+  // items of one token are adjacent, from key 0 on: alone if the next item
+  // starts at key 0 again
+  const bool alone = it.k0 == 0 && (idx + 1 == n_items || items[idx + 1].k0 == 0);
+  const int G = n_q / n_kv, row = lane & 15;
+  RowState st;
+  f32x4_t oacc[D / 16];
+  decode_blocks<D>(q, kv, n_kv, tabs, it, kvh, n_q, it.k0 / kBlock, (it.k1 + kBlock - 1) / kBlock,
+                   st, oacc);
+  if (row >= G) return;
   if (alone) {
     const float inv = 1.0f / st.l;
     bf16_t* out = (bf16_t*)tabs.attn_out;
@@ -262,6 +276,54 @@ __global__ __launch_bounds__(256) void attn_decode_bf16(const bf16_t* __restrict
   if (lane < 16) {
     part_ml[ob * 2 + 0] = st.m;
     part_ml[ob * 2 + 1] = st.l;
+  }
+}
+
+// Items that hold all keys of their token, one workgroup of kItemWaves waves
+// per (item, kv head): each wave takes an eighth of the blocks and the parts
+// meet in LDS, so that a small step of middling contexts needs neither
+// partials in memory nor the merge's launch. (Not for long contexts or large
+// batches, where splits of equal size over the whole chip balance better.)
+constexpr int kItemWaves = 8;
+
+template <int D>
+__global__ __launch_bounds__(kItemWaves * 64) void attn_decode_item_bf16(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ kv, int n_kv, SegTables tabs,
+    const DecodeItem* __restrict__ items, const int32_t* __restrict__ order, int n_q) {
+  constexpr int NW = kItemWaves;
+  __shared__ float2 s_ml[NW][16];
+  __shared__ f32x4_t s_o[NW][16][D / 4 + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kvh = blockIdx.y, G = n_q / n_kv, row = lane & 15;
+  const DecodeItem it = items[order[blockIdx.x]];
+  const int nb = (it.k1 + kBlock - 1) / kBlock, per = (nb + NW - 1) / NW;
+  RowState st;
+  f32x4_t oacc[D / 16];
+  decode_blocks<D>(q, kv, n_kv, tabs, it, kvh, n_q, min(wave * per, nb), min((wave + 1) * per, nb),
+                   st, oacc);
+  if (lane < 16) s_ml[wave][row] = make_float2(st.m, st.l);
+#pragma unroll
+  for (int t = 0; t < D / 16; ++t) s_o[wave][row][t * 4 + (lane >> 4)] = oacc[t];
+  __syncthreads();
+  for (int e = threadIdx.x; e < G * D / 4; e += NW * 64) {
+    const int r = e / (D / 4), c = e % (D / 4);
+    float M = s_ml[0][r].x;  // wave 0 has at least one block
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, s_ml[w][r].x);
+    float l = 0.f;
+    f32x4_t o = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float f = exp2f(s_ml[w][r].x - M);
+      l += f * s_ml[w][r].y;
+      o += f * s_o[w][r][c];
+    }
+    o *= 1.0f / l;
+    u32x2_t v;
+    v[0] = pack_bf16x2(o[0], o[1]);
+    v[1] = pack_bf16x2(o[2], o[3]);
+    *(u32x2_t*)((bf16_t*)tabs.attn_out +
+                packed_a_offset(it.tok, (kvh * G + r) * D + 4 * c, n_q * D)) = v;
   }
 }
 
@@ -959,6 +1021,18 @@ hipError_t attn_decode(DType dt, const void* q, KVLayer kv, SegTables tabs,
                        float* part_o, float* part_ml, hipStream_t s) {
   if (n_items == 0) return hipSuccess;
   if (dt != DT_BF16) return hipErrorInvalidValue;
+  if (tabs.whole_items) {
+    const dim3 g(n_items, kv.n_kv);
+    if (kv.head_dim == 128)
+      attn_decode_item_bf16<128><<<g, kItemWaves * 64, 0, s>>>(
+          (const bf16_t*)q, (const bf16_t*)kv.base, kv.n_kv, tabs, items, order, n_q);
+    else if (kv.head_dim == 64)
+      attn_decode_item_bf16<64><<<g, kItemWaves * 64, 0, s>>>(
+          (const bf16_t*)q, (const bf16_t*)kv.base, kv.n_kv, tabs, items, order, n_q);
+    else
+      return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
   dim3 grid(n_items, (kv.n_kv + 3) / 4);
   if (kv.head_dim == 128)
     attn_decode_bf16<128><<<grid, 256, 0, s>>>((const bf16_t*)q, (const bf16_t*)kv.base, kv.n_kv,

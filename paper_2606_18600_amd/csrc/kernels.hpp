@@ -52,6 +52,7 @@ struct SegTables {
   const int32_t* bt1;
   int32_t stride1;
   void* attn_out = nullptr;
+  bool whole_items = false;  // decode: every item holds all keys of its token, several waves each
   PrefillParts parts{};
 };
 

@@ -45,6 +45,17 @@ constexpr int kRing = 4;             // pinned staging buffers in flight
 constexpr int kMaxSplits = 32;       // decode key splits per sequence, at most
 constexpr int kSplitMinBlocks = 4;   // at least 4 blocks (64 keys) per split
 constexpr int kSplitNoneBlocks = 8;  // a step with no more blocks than this per token: no splits
+// A step of at most kWholePairs (token, kv head) pairs with at most this many
+// blocks per token: a workgroup per pair whose waves share the blocks, instead
+// of splits and their merge. A pair's keys then pass through one CU, so with
+// fewer than half of the CUs at work only short contexts gain (one rank of 8,
+// per layer: 16 pairs of 19 blocks 2.5 us less, 16 pairs of 63 blocks 3.3 us
+// more, 128 pairs of up to 63 blocks 6 us less; 400 pairs of them 2.5 us less
+// on the 32B shape).
+constexpr int kWholePairs = 512;
+int whole_blocks(long long pairs) {
+  return pairs > kWholePairs ? 0 : pairs >= 128 ? 64 : 32;
+}
 constexpr int kSkinnyMaxRows = 128;  // decode-sized steps use split-K GEMMs
 constexpr int kMaxKvSplits = 4;      // K splits of the key/value columns of a prefill QKV
 constexpr int kMaxMidSplits = 8;     // K splits of the products of a small tiled step
@@ -297,6 +308,7 @@ struct StepMeta {
   PrefillItem* pitems;
   int n_ditems = 0, n_pitems = 0;
   size_t ints = 0;  // int32 values in all
+  bool whole_items = false;  // decode items are whole tokens for several waves
 };
 
 // The same arrays at another base (the device copy of the host staging).
@@ -370,7 +382,11 @@ bool build_meta(const stage* st, const stage_batch* pf, const stage_batch* dc, i
   const int waves = decode_waves(st->attn_waves, nd, st->attn_scale);
   // Short contexts only: unsplit, which saves the merge of the splits (2.1 us
   // and a launch per layer, against a chain of at most 4 more blocks).
-  const int bps_min = longest <= kSplitNoneBlocks ? kSplitNoneBlocks : kSplitMinBlocks;
+  m.whole_items = longest > kSplitNoneBlocks &&
+                  longest <= whole_blocks((long long)nd * st->cfg.n_kv_heads);
+  const int bps_min = m.whole_items                 ? longest
+                      : longest <= kSplitNoneBlocks ? kSplitNoneBlocks
+                                                    : kSplitMinBlocks;
   const int bps_target = (int)std::max<long long>(bps_min, (units + waves - 1) / waves);
   // The workspace holds kMaxSplits splits per sequence of a small stage; a
   // step of few sequences on a larger one may use the others' room (three
@@ -630,7 +646,7 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
   const int Tp = T - nd;
   SegTables tabs{pf && np ? pf->block_tables : nullptr, pf && np ? pf->max_blocks_per_seq : 0, np,
                  dc && nd ? dc->block_tables : nullptr, dc && nd ? dc->max_blocks_per_seq : 0,
-                 st->ws + st->r_attn.off};
+                 st->ws + st->r_attn.off, hm.whole_items};
 
   if (dt == DT_BF16 && hm.n_pitems > 0) {
     // the projections have been read when attention runs: their place holds

@@ -1,7 +1,8 @@
 """Decode attention over key splits: tokens with one split (written by the
 attention kernel itself) next to tokens with many, at batch sizes on both
 sides of each choice of the merge kernel's waves per token, for several group
-sizes; and steps whose contexts are all too short to be split."""
+sizes; steps whose contexts are all too short to be split; and steps whose
+tokens are each taken whole by the waves of one workgroup."""
 
 from __future__ import annotations
 
@@ -25,12 +26,17 @@ def _shape(nq, nkv, d):
     (8, 1, 128, 3, 1500),    # 8 waves per token, up to 24 splits
     (8, 1, 128, 1, 6000),    # one token, 94 splits
     (16, 1, 128, 5, 900),    # group 16: 4 waves
-    (4, 4, 64, 32, 300),     # 128 (token, kv head) pairs: 8 waves
-    (8, 4, 64, 33, 300),     # 132: 4 waves
-    (8, 2, 128, 128, 300),   # 256: 4 waves
-    (4, 2, 64, 129, 300),    # 258: 1 wave
-    (2, 2, 128, 7, 127),     # at most 8 blocks: unsplit, no merge
-    (4, 2, 64, 7, 128),      # 9 blocks: split
+    (4, 4, 64, 32, 1100),    # 128 (token, kv head) pairs: 8 waves
+    (8, 4, 64, 33, 1100),    # 132: 4 waves
+    (8, 2, 128, 128, 1100),  # 256: 4 waves
+    (4, 4, 64, 129, 300),    # 516: 1 wave
+    (2, 2, 128, 7, 127),     # at most 8 blocks: unsplit, one wave per token
+    (4, 2, 64, 7, 128),      # 9 blocks: whole tokens, 8 waves each
+    (8, 1, 128, 5, 511),     # 32 blocks: whole
+    (8, 1, 128, 5, 512),     # 33 blocks on few pairs: split
+    (8, 4, 64, 32, 1023),    # 64 blocks on 128 pairs: whole
+    (16, 1, 128, 130, 200),  # group 16, whole
+    (4, 4, 128, 128, 200),   # 512 pairs: whole
 ])
 def test_decode_over_splits(nq, nkv, d, seqs, longest):
     """One layer against the exact oracle over a random cache. The decode
