@@ -63,7 +63,8 @@ int stream_splits(int N, int K, int max_splits, bool swiglu) {
   int s = 1;
   if (!swiglu) {
     s = std::max(1, std::min({kStreamBlocks / (per * groups), max_splits, K / 256}));
-    const int kb = K % 128 == 0 ? skinny_kp_kb_len(K, s) : skinny_kb_len(K, s);
+    // the K ranges the launcher will take (gemm_skinny)
+    const int kb = skinny_kp_used(K, s, false) ? skinny_kp_kb_len(K, s) : skinny_kb_len(K, s);
     s = (K + kb - 1) / kb;
   }
   const int frags = stream_fragments(1, N, K, s, swiglu);
