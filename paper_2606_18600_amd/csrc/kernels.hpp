@@ -198,6 +198,47 @@ constexpr int kGemvRows = 8;
 hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int N, int K,
                 void* out, hipStream_t s, RopeRows rope = RopeRows{});
 
+// A bf16 stage as the sizing rules of its tiled steps (more rows than the
+// split-K decode GEMMs take) see it.
+struct TiledShape {
+  int hidden = 0, qw = 0, qkvw = 0, ffn = 0;  // H, query columns, QKV columns, F
+  int max_tokens = 0;
+  int tail_rows = 0;        // last rows that the skinny kernels may take (0: never)
+  int cus = 256;
+  size_t gate_up_room = 0;  // fp32 values that a gate-up product's planes may take
+};
+constexpr int kMaxMidSplits = 8;         // K splits of the products of a small tiled step
+constexpr int kMidRows = 2048;           // partial-plane rows of such a step (splits x T) ...
+constexpr size_t kMidElems = 16u << 20;  // ... or this many fp32 values, if more (narrow N)
+// fp32 values the partial planes of a small tiled step's [T, N] product may
+// take (T <= max_tokens): kMidRows rows, or for narrow products (tensor-
+// parallel shards, whose 256-wide tiles need more K ranges to fill a round)
+// up to kMidElems values, as far as kMaxMidSplits planes of max_tokens rows
+// need them.
+size_t mid_capacity(int max_tokens, int N);
+// K splits for the [T, N] x [N, K]^T QKV, O or down product of a tiled step,
+// or 0. When its 256 x 256 tiles would occupy at most half of the CUs for the
+// whole K (e.g. O and down with 32 tiles per 256 rows), it runs over K ranges
+// into fp32 partial planes that the consumer sums (as in decode steps): as
+// many ranges (a power of two, at most 8) as keep the launch within one round
+// and the planes within mid_capacity.
+int mid_splits(const TiledShape& t, int T, int N, int K);
+// K splits of the gate-up product of such a step, or 0. Its SwiGLU then needs
+// a pass over the planes, so the ranges are weighed. The planes lie where the
+// QKV projection was.
+int gate_up_splits(const TiledShape& t, int T);
+// Rows of a large step past its last multiple of 256 (at most tail_rows of
+// them): the candidates for the split-K skinny kernels (row_tail_for), with
+// the rows before them on whole tiles. Only when the whole-tile part needs no
+// K splits of its own.
+int row_tail(const TiledShape& t, int T);
+// Whether a product with N columns (N of them in 256-wide tiles; for QKV with
+// split key/value columns, the query columns) runs its last rt rows on the
+// skinny kernel: only when those rows' extra 256-row tiles would add a round
+// of workgroups (a mostly idle one: the product then costs about one more
+// round of tiles, against one HBM-bound pass over its weights).
+bool row_tail_for(const TiledShape& t, int T, int rt, int N);
+
 // Decode attention: items are taken in the host's dispatch order (order[0]
 // first). An item that holds all keys of its token writes the finished row to
 // tabs.attn_out; the others write partials at their own index.

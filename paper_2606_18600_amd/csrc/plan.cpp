@@ -1,6 +1,8 @@
-// Host-side sizing rules shared by the launchers and the stage runtime: how
-// many K ranges a split-K decode GEMM takes and how many positions one
-// prefill attention work item covers. Plain host code (no HIP calls).
+// Host-side sizing rules shared by the launchers and the stage runtime: the K
+// ranges of decode products and the kernel of those of at most 32 rows, the K
+// ranges of small tiled steps and the last rows of large ones, and the
+// positions of a prefill attention work item and the split of its keys. Plain
+// host code (no HIP calls).
 #include <algorithm>
 #include <cstdlib>
 
@@ -95,6 +97,61 @@ PrefillParts prefill_split(int n_items, int n_kv, long long total, int longest, 
       return PrefillParts{buf, (int32_t)stages, (int32_t)most};
   }
   return PrefillParts{};
+}
+
+size_t mid_capacity(int max_tokens, int N) {
+  return std::max((size_t)kMidRows * N,
+                  std::min(kMidElems, (size_t)kMaxMidSplits * max_tokens * N));
+}
+
+// (Exactly half of the CUs, 900 rows of the 70B shape: O and down 165 and 515
+// us on one full round of 128 x 128 tiles, 110 and 344 in two ranges, and
+// about 10 more in each RMSNorm.)
+int mid_splits(const TiledShape& t, int T, int N, int K) {
+  if (N % 256 != 0) return 0;
+  const int tiles = (T + 255) / 256 * (N / 256);
+  if (2 * tiles > t.cus) return 0;
+  int best = 0;
+  for (int sp = 2; sp <= kMaxMidSplits; sp *= 2)
+    if (tiles * sp <= t.cus && K % (64 * sp) == 0 &&
+        (size_t)sp * T * N <= mid_capacity(t.max_tokens, N))
+      best = sp;
+  return best;
+}
+
+// One range of K on 256-row tiles takes about K / 55 us (192 rows and fewer:
+// K / 64), the planes are written and read at about 4 TB/s, the pass adds 3
+// us. (A rank's share of the FFN: at 2 F = 7168, H = 8192 150 rows took 88 us
+// unsplit, 600 rows 113; at 14336, 400 rows 148.)
+int gate_up_splits(const TiledShape& t, int T) {
+  const int N = 2 * t.ffn, K = t.hidden;
+  if (N % 256 != 0) return 0;
+  const long tiles = (long)(T + 255) / 256 * (N / 256);
+  const double range = T <= 192 ? K / 64.0 : K / 55.0;
+  int best = 0;
+  double cost = range;
+  for (int sp = 2; sp <= kMaxMidSplits; sp *= 2) {
+    if (tiles * sp > t.cus || K % (64 * sp) != 0 || (size_t)sp * T * N > t.gate_up_room) break;
+    const double c = range / sp + 2.0 * sp * T * N * 4 / 4e6 + 3;
+    if (c < cost) best = sp, cost = c;
+  }
+  return best;
+}
+
+int row_tail(const TiledShape& t, int T) {
+  const int rt = T % 256, T0 = T - rt;
+  if (rt == 0 || rt > t.tail_rows || T0 < 256) return 0;
+  if (mid_splits(t, T0, t.qkvw, t.hidden) || mid_splits(t, T0, t.hidden, t.qw) ||
+      mid_splits(t, T0, t.hidden, t.ffn))
+    return 0;
+  return rt;
+}
+
+bool row_tail_for(const TiledShape& t, int T, int rt, int N) {
+  if (rt == 0 || N % 256 != 0) return false;
+  const long cols = N / 256;
+  const long with = (T + 255) / 256 * cols, without = (T - rt) / 256 * cols;
+  return (with + t.cus - 1) / t.cus > (without + t.cus - 1) / t.cus;
 }
 
 int prefill_item_positions(DType dt, int group) {

@@ -58,19 +58,6 @@ int whole_blocks(long long pairs) {
 }
 constexpr int kSkinnyMaxRows = 128;  // decode-sized steps use split-K GEMMs
 constexpr int kMaxKvSplits = 4;      // K splits of the key/value columns of a prefill QKV
-constexpr int kMaxMidSplits = 8;     // K splits of the products of a small tiled step
-constexpr int kMidRows = 2048;       // partial-plane rows of such a step (splits x T) ...
-constexpr size_t kMidElems = 16u << 20;  // ... or this many fp32 values, if more (narrow N)
-
-// fp32 values the partial planes of a small tiled step's [T, N] product may
-// take (T <= max_tokens): kMidRows rows, or for narrow products (tensor-
-// parallel shards, whose 256-wide tiles need more K ranges to fill a round)
-// up to kMidElems values, as far as kMaxMidSplits planes of max_tokens rows
-// need them.
-size_t mid_capacity(int max_tokens, int N) {
-  return std::max((size_t)kMidRows * N,
-                  std::min(kMidElems, (size_t)kMaxMidSplits * max_tokens * N));
-}
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -460,76 +447,19 @@ int qkv_kv_splits(const stage* st, int T) {
   return 0;
 }
 
-// K splits for an [T, N] x [N, K]^T product of a bf16 tiled step (more rows
-// than the split-K decode GEMMs take), or 0. When its 256 x 256 tiles would
-// occupy at most half of the CUs for the whole K (e.g. O and down with 32
-// tiles per 256 rows), it runs over K ranges into fp32 partial planes that
-// the consumer sums (as in decode steps): as many ranges (a power of two, at
-// most 8) as keep the launch within one round and the planes within
-// kMidRows rows. (Exactly half, 900 rows of the 70B shape: O and down 165 and
-// 515 us on one full round of 128 x 128 tiles, 110 and 344 in two ranges,
-// and about 10 more in each RMSNorm.)
-int mid_splits(const stage* st, int T, int N, int K) {
-  if (st->cfg.dtype != STAGE_BF16 || T <= st->skinny_rows || N % 256 != 0) return 0;
-  const int tiles = (T + 255) / 256 * (N / 256);
-  if (2 * tiles > st->cus) return 0;
-  int best = 0;
-  for (int sp = 2; sp <= kMaxMidSplits; sp *= 2)
-    if (tiles * sp <= st->cus && K % (64 * sp) == 0 &&
-        (size_t)sp * T * N <= mid_capacity(st->max_tokens, N))
-      best = sp;
-  return best;
-}
-
-// K splits of the gate-up product of such a step, or 0. Its SwiGLU then needs
-// a pass over the planes, so the ranges are weighed: one range of K on 256-row
-// tiles takes about K / 55 us (192 rows and fewer: K / 64), the planes are
-// written and read at about 4 TB/s, the pass adds 3 us. The planes lie where
-// the QKV projection was. (A rank's share of the FFN: at 2 F = 7168, H = 8192
-// 150 rows took 88 us unsplit, 600 rows 113; at 14336, 400 rows 148.)
-int gate_up_splits(const stage* st, int T) {
-  const int N = 2 * st->cfg.ffn, K = st->cfg.hidden;
-  if (st->cfg.dtype != STAGE_BF16 || T <= st->skinny_rows || N % 256 != 0) return 0;
-  const long tiles = (long)(T + 255) / 256 * (N / 256);
-  const double range = T <= 192 ? K / 64.0 : K / 55.0;
-  int best = 0;
-  double cost = range;
-  for (int sp = 2; sp <= kMaxMidSplits; sp *= 2) {
-    if (tiles * sp > st->cus || K % (64 * sp) != 0 ||
-        (size_t)sp * T * N * 4 > st->r_qkv.bytes)
-      break;
-    const double c = range / sp + 2.0 * sp * T * N * 4 / 4e6 + 3;
-    if (c < cost) best = sp, cost = c;
-  }
-  return best;
-}
-
-// Rows of a large bf16 step past its last multiple of 256 (at most the
-// skinny limit of them): the candidates for the split-K skinny kernels
-// (row_tail_for), with the rows before them on whole tiles. Only when the
-// whole-tile part needs no K splits of its own.
-int row_tail(const stage* st, int T) {
-  if (st->cfg.dtype != STAGE_BF16 || T <= st->skinny_rows || !st->row_tail_on) return 0;
-  const int rt = T % 256, T0 = T - rt;
-  if (rt == 0 || rt > st->skinny_rows || T0 < 256) return 0;
+// What the sizing rules of a tiled step (plan.cpp) look at.
+TiledShape tiled_shape(const stage* st) {
   const auto& c = st->cfg;
-  const int qw = c.n_q_heads * c.head_dim, qkvw = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
-  if (mid_splits(st, T0, qkvw, c.hidden) || mid_splits(st, T0, c.hidden, qw) ||
-      mid_splits(st, T0, c.hidden, c.ffn))
-    return 0;
-  return rt;
-}
-
-// Whether a product with N tile columns (N of them in 256-wide tiles; for
-// QKV with split key/value columns, the query columns) runs its last rt rows
-// on the skinny kernel: only when those rows' extra 256-row tiles would add
-// a round of workgroups (a mostly idle one: the product then costs about one
-// more round of tiles, against one HBM-bound pass over its weights).
-bool row_tail_for(const stage* st, int T, int rt, int N) {
-  if (rt == 0 || N % 256 != 0) return false;
-  const long cols = N / 256;
-  const long with = (T + 255) / 256 * cols, without = (T - rt) / 256 * cols;
-  return (with + st->cus - 1) / st->cus > (without + st->cus - 1) / st->cus;
+  TiledShape t;
+  t.hidden = c.hidden;
+  t.qw = c.n_q_heads * c.head_dim;
+  t.qkvw = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+  t.ffn = c.ffn;
+  t.max_tokens = st->max_tokens;
+  t.tail_rows = st->row_tail_on ? st->skinny_rows : 0;
+  t.cus = st->cus;
+  t.gate_up_room = st->r_qkv.bytes / 4;
+  return t;
 }
 
 // Take the next pinned staging slot of the ring, waiting until the upload
@@ -679,10 +609,12 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
   // (which reads hidden_in) is launched before it.
   // rows [T0, T) of a large step may run on the skinny kernels (row_tail):
   // for each of QKV, O and down separately (rq, ro, rd: 0 or rt)
-  const int rt = skinny ? 0 : row_tail(st, T), T0 = T - rt;
+  const TiledShape ts = tiled_shape(st);
+  const bool tiled = dt == DT_BF16 && !skinny;
+  const int rt = tiled ? row_tail(ts, T) : 0, T0 = T - rt;
   const int kv_splits0 = rt ? qkv_kv_splits(st, T0) : 0;
-  const int rq = row_tail_for(st, T, rt, kv_splits0 ? qw : qkvw) ? rt : 0;
-  const int ro = row_tail_for(st, T, rt, H) ? rt : 0, rd = ro;
+  const int rq = row_tail_for(ts, T, rt, kv_splits0 ? qw : qkvw) ? rt : 0;
+  const int ro = row_tail_for(ts, T, rt, H) ? rt : 0, rd = ro;
   const int Tq = T - rq, To = T - ro, Td = T - rd;  // rows of each product on tiles
   const int kv_splits = skinny ? 0 : qkv_kv_splits(st, Tq);
   // with split key/value columns the query product applies RoPE (after the
@@ -691,8 +623,9 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
   const bool q_fused = kv_splits > 0 && (!c.qk_norm || st->q_norm_fused) && D == 128 &&
                        nq % 4 == 0 &&
                        st->q_rope_fused;
-  const int mq = rt ? 0 : mid_splits(st, T, qkvw, H), mo = rt ? 0 : mid_splits(st, T, H, qw),
-            md = rt ? 0 : mid_splits(st, T, H, F), mg = rt ? 0 : gate_up_splits(st, T);
+  const bool mid = tiled && rt == 0;
+  const int mq = mid ? mid_splits(ts, T, qkvw, H) : 0, mo = mid ? mid_splits(ts, T, H, qw) : 0,
+            md = mid ? mid_splits(ts, T, H, F) : 0, mg = mid ? gate_up_splits(ts, T) : 0;
   // the tail rows of the packed activations (whole 16-row fragments)
   auto tail_rows = [&](const void* act, int K) -> const void* {
     return (const uint16_t*)act + (size_t)(T0 / 16) * (K / 32) * 512;

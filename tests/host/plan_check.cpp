@@ -1,0 +1,112 @@
+// CPU check of the library's sizing rules (plan.cpp; test code only). Built
+// with g++ against the host-only stand-in of the HIP runtime header; one
+// named check per run, exit status 0 and a last line "ok" on success.
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <initializer_list>
+
+#include "../../paper_2606_18600_amd/csrc/kernels.hpp"
+
+using namespace stage_k;
+
+#define CHECK(c, ...)                                              \
+  do {                                                             \
+    if (!(c)) {                                                    \
+      std::fprintf(stderr, "line %d: %s: ", __LINE__, #c);         \
+      std::fprintf(stderr, __VA_ARGS__);                           \
+      std::fprintf(stderr, "\n");                                  \
+      std::exit(1);                                                \
+    }                                                              \
+  } while (0)
+
+namespace {
+
+int up(int a, int b) { return (a + b - 1) / b; }
+
+// Key split of prefill attention: parts within the grid and the buffer, every
+// part not empty and starting no later than its item's first position.
+void prefill_parts_check() {
+  int split = 0, whole = 0;
+  for (int d : {64, 128})
+    for (int n_kv : {1, 2, 8})
+      for (int items : {1, 2, 5, 16, 61, 300})
+        for (int longest : {1, 4, 9, 17, 40, 96, 400, 1000})
+          for (size_t room : {(size_t)0, (size_t)1 << 16, (size_t)1 << 20, (size_t)1 << 26}) {
+            float buf;
+            const long long total = (long long)items * (longest + 1) / 2 + longest / 2;
+            const PrefillParts p = prefill_split(items, n_kv, total, longest, d, &buf, room);
+            if (p.stages == 0) {
+              ++whole;
+              CHECK(p.most == 1, "no split has one part");
+              continue;
+            }
+            ++split;
+            CHECK((size_t)items * n_kv * p.most * prefill_part_floats(d) <= room, "buffer");
+            for (int nst = 1; nst <= longest; ++nst)
+              for (int npos : {1, 16, 64, 128}) {
+                const int p0 = nst * kPrefillStage - npos;  // an item of nst stages
+                if (p0 < 0) continue;
+                const int parts = prefill_parts(p.stages, p0, nst);
+                CHECK(parts >= 1 && parts <= p.most, "%d of %d parts", parts, p.most);
+                CHECK((parts - 1) * p.stages < nst, "empty part");
+                CHECK((parts - 1) * p.stages * kPrefillStage <= p0, "part past position %d", p0);
+              }
+          }
+  CHECK(split > 100 && whole > 100, "%d split, %d whole", split, whole);
+  // few chunks behind long prefixes are split, many or short ones are not
+  float buf;
+  const size_t room = (size_t)1 << 26;
+  CHECK(prefill_split(1, 1, 64, 64, 128, &buf, room).most > 1, "one position behind 4000 keys");
+  CHECK(prefill_split(4, 2, 4 * 95, 95, 128, &buf, room).most > 1, "64 behind 6000, two kv heads");
+  CHECK(prefill_split(12, 8, 12 * 58, 58, 128, &buf, room).most > 1, "191 behind 3535, 8 heads");
+  CHECK(prefill_split(128, 8, 128 * 960, 960, 128, &buf, room).stages == 0, "2048 behind 61440");
+  CHECK(prefill_split(25, 8, 25 * 4, 7, 128, &buf, room).stages == 0, "400 rows of one prompt");
+}
+
+// Products of at most 32 rows: the planned K ranges are what the launcher
+// takes (every range not empty), never more than the plan they replace, and
+// the stream kernel is chosen at the shapes made for it.
+void stream_check() {
+  int taken = 0;
+  for (int N = 64; N <= 65536; N += N < 4096 ? 64 : 1088)
+    for (int K = 64; K <= 28672; K += K < 1024 ? 64 : 896)
+      for (int most : {1, 2, 5, 8, 32}) {
+        if (N % 64 || K % 64) continue;
+        const int s = stream_splits(N, K, most, false);
+        if (s == 0) continue;
+        ++taken;
+        CHECK(s >= 1 && s <= most, "N %d K %d: %d of %d ranges", N, K, s, most);
+        const int kb = skinny_kp_used(K, s, false) ? skinny_kp_kb_len(K, s) : skinny_kb_len(K, s);
+        CHECK(up(K, kb) == s, "N %d K %d: %d ranges of %d", N, K, s, kb);
+        for (int M : {1, 16, 17, 32}) {
+          const int f = stream_fragments(M, N, K, s, false);
+          CHECK(f == 2 || f == 4, "N %d K %d M %d", N, K, M);
+          CHECK(N / 64 * s * (f == 2 ? 2 : 1) <= kStreamBlocks, "blocks");
+        }
+      }
+  CHECK(taken > 1000, "%d plans", taken);
+  for (int N : {1280, 512, 1408}) CHECK(stream_fragments(32, N, 704, 1, false) == 2, "N %d", N);
+  CHECK(stream_splits(8192, 512, 8, false) == 2, "two K ranges of 256");
+  CHECK(stream_fragments(1, 8192, 512, 2, false) == 4, "whole groups");
+  CHECK(stream_fragments(32, 8320, 256, 1, true) == 4, "SwiGLU of 130 groups");
+  CHECK(stream_fragments(16, 16512, 384, 1, true) == 4, "SwiGLU of 258 groups, 16 rows");
+  CHECK(stream_fragments(17, 16512, 384, 1, true) == 0, "SwiGLU of 258 groups, 17 rows");
+  CHECK(stream_fragments(33, 512, 256, 1, false) == 0, "33 rows");
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const char* name = argc > 1 ? argv[1] : "";
+  if (!std::strcmp(name, "prefill_parts"))
+    prefill_parts_check();
+  else if (!std::strcmp(name, "stream"))
+    stream_check();
+  else
+    return 2;
+  std::puts("ok");
+  return 0;
+}
