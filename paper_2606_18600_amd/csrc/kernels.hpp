@@ -217,11 +217,11 @@ constexpr size_t kMidElems = 16u << 20;  // ... or this many fp32 values, if mor
 // need them.
 size_t mid_capacity(int max_tokens, int N);
 // K splits for the [T, N] x [N, K]^T QKV, O or down product of a tiled step,
-// or 0. When its 256 x 256 tiles would occupy at most half of the CUs for the
-// whole K (e.g. O and down with 32 tiles per 256 rows), it runs over K ranges
-// into fp32 partial planes that the consumer sums (as in decode steps): as
-// many ranges (a power of two, at most 8) as keep the launch within one round
-// and the planes within mid_capacity.
+// or 0. When its 256 x 256 tiles would occupy less than half of the CUs for
+// the whole K (e.g. O and down with 32 tiles per 256 rows), or exactly half of
+// them for a long K, it runs over K ranges into fp32 partial planes that the
+// consumer sums (as in decode steps): as many ranges (a power of two, at most
+// 8) as keep the launch within one round and the planes within mid_capacity.
 int mid_splits(const TiledShape& t, int T, int N, int K);
 // K splits of the gate-up product of such a step, or 0. Its SwiGLU then needs
 // a pass over the planes, so the ranges are weighed. The planes lie where the

@@ -104,13 +104,17 @@ size_t mid_capacity(int max_tokens, int N) {
                   std::min(kMidElems, (size_t)kMaxMidSplits * max_tokens * N));
 }
 
-// (Exactly half of the CUs, 900 rows of the 70B shape: O and down 165 and 515
-// us on one full round of 128 x 128 tiles, 110 and 344 in two ranges, and
-// about 10 more in each RMSNorm.)
+// At exactly half of the CUs 128 x 128 tiles would fill their two slots per
+// CU, and what two ranges save grows with K while their planes cost the same
+// (product and RMSNorm, one range -> two, at 900 x 8192 / 1800 x 4096: K =
+// 1024 45 -> 50 / 37 -> 51 us, 2048 63 -> 61 / 54 -> 62, 3584 90 -> 76 / 79 ->
+// 78, 8192 162 -> 125 / 151 -> 126, 28672 528 -> 361 / 514 -> 364): split from
+// kHalfRoundK on.
 int mid_splits(const TiledShape& t, int T, int N, int K) {
+  constexpr int kHalfRoundK = 3072;
   if (N % 256 != 0) return 0;
   const int tiles = (T + 255) / 256 * (N / 256);
-  if (2 * tiles > t.cus) return 0;
+  if (2 * tiles > t.cus || (2 * tiles == t.cus && K < kHalfRoundK)) return 0;
   int best = 0;
   for (int sp = 2; sp <= kMaxMidSplits; sp *= 2)
     if (tiles * sp <= t.cus && K % (64 * sp) == 0 &&

@@ -97,6 +97,34 @@ void stream_check() {
   CHECK(stream_fragments(33, 512, 256, 1, false) == 0, "33 rows");
 }
 
+TiledShape shape(int H, int nq, int nkv, int d, int F) {
+  TiledShape t;
+  t.hidden = H;
+  t.qw = nq * d;
+  t.qkvw = (nq + 2 * nkv) * d;
+  t.ffn = F;
+  t.max_tokens = 2176;
+  t.tail_rows = 128;
+  t.gate_up_room = mid_capacity(t.max_tokens, t.qkvw);
+  return t;
+}
+
+// Products whose tiles fill exactly half of the CUs are split for a long K
+// only; fewer tiles split whatever K is.
+void half_round_check() {
+  const TiledShape t = shape(8192, 64, 8, 128, 28672);
+  struct { int T, N; } half[] = {{769, 8192}, {1024, 8192}, {1793, 4096}, {2048, 4096}, {200, 32768}};
+  for (auto h : half) {
+    for (int K : {512, 1024, 2048}) CHECK(mid_splits(t, h.T, h.N, K) == 0, "%d x %d K %d", h.T, h.N, K);
+    if (h.N <= 8192)
+      for (int K : {3584, 4096, 8192, 28672})
+        CHECK(mid_splits(t, h.T, h.N, K) == 2, "%d x %d K %d", h.T, h.N, K);
+  }
+  CHECK(mid_splits(t, 768, 8192, 1024) == 2, "96 tiles");
+  CHECK(mid_splits(t, 256, 8192, 1024) == 8, "32 tiles");
+  CHECK(mid_splits(t, 1025, 8192, 28672) == 0, "160 tiles");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -105,6 +133,8 @@ int main(int argc, char** argv) {
     prefill_parts_check();
   else if (!std::strcmp(name, "stream"))
     stream_check();
+  else if (!std::strcmp(name, "half_round"))
+    half_round_check();
   else
     return 2;
   std::puts("ok");
