@@ -229,8 +229,8 @@ int mid_splits(const TiledShape& t, int T, int N, int K);
 int gate_up_splits(const TiledShape& t, int T);
 // Rows of a large step past its last multiple of 256 (at most tail_rows of
 // them): the candidates for the split-K skinny kernels (row_tail_for), with
-// the rows before them on whole tiles. Only when the whole-tile part needs no
-// K splits of its own.
+// the rows before them on whole tiles. Only when no product of the whole-tile
+// part fills less than half of the CUs and is split over K for it.
 int row_tail(const TiledShape& t, int T);
 // Whether a product with N columns (N of them in 256-wide tiles; for QKV with
 // split key/value columns, the query columns) runs its last rt rows on the

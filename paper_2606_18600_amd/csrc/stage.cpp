@@ -625,7 +625,8 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
                        st->q_rope_fused;
   const bool mid = tiled && rt == 0;
   const int mq = mid ? mid_splits(ts, T, qkvw, H) : 0, mo = mid ? mid_splits(ts, T, H, qw) : 0,
-            md = mid ? mid_splits(ts, T, H, F) : 0, mg = mid ? gate_up_splits(ts, T) : 0;
+            md = mid ? mid_splits(ts, T, H, F) : 0;
+  const int mg = tiled ? gate_up_splits(ts, T) : 0;  // (gate-up runs no row tail of this kind)
   // the tail rows of the packed activations (whole 16-row fragments)
   auto tail_rows = [&](const void* act, int K) -> const void* {
     return (const uint16_t*)act + (size_t)(T0 / 16) * (K / 32) * 512;

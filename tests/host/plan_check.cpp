@@ -125,6 +125,29 @@ void half_round_check() {
   CHECK(mid_splits(t, 1025, 8192, 28672) == 0, "160 tiles");
 }
 
+// Rows past the last whole row of tiles: a step whose whole tiles fill exactly
+// half of the CUs (or more) in O and down keeps its tail, one whose whole tiles
+// fill less is split over K instead.
+void row_tail_check() {
+  struct { TiledShape t; int T, rows; bool qkv; } cases[] = {
+      {shape(8192, 64, 32, 128, 22016), 1025, 1, true},   // QKV: 256 tiles of 1024 rows
+      {shape(8192, 64, 32, 128, 22016), 1152, 128, true},
+      {shape(8192, 64, 32, 128, 22016), 1153, 0, false},  // more rows than the skinny kernels take
+      {shape(4096, 32, 16, 128, 14336), 2049, 1, true},
+      {shape(4096, 32, 16, 128, 14336), 2176, 128, true},
+      {shape(8192, 64, 8, 128, 28672), 1100, 76, false},
+      {shape(8192, 64, 8, 128, 28672), 2176, 128, false},  // 320 or 360 tiles: two rounds either way
+      {shape(8192, 64, 8, 128, 28672), 800, 0, false},    // O, down: 96 tiles of 768 rows
+      {shape(8192, 64, 8, 128, 28672), 200, 0, false},    // no whole row of tiles
+      {shape(8192, 64, 8, 128, 28672), 2048, 0, false},
+  };
+  for (auto& c : cases) {
+    const int rt = row_tail(c.t, c.T);
+    CHECK(rt == c.rows, "H %d T %d: %d rows", c.t.hidden, c.T, rt);
+    CHECK(row_tail_for(c.t, c.T, rt, c.t.qkvw) == c.qkv, "H %d T %d", c.t.hidden, c.T);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -135,6 +158,8 @@ int main(int argc, char** argv) {
     stream_check();
   else if (!std::strcmp(name, "half_round"))
     half_round_check();
+  else if (!std::strcmp(name, "row_tail"))
+    row_tail_check();
   else
     return 2;
   std::puts("ok");
