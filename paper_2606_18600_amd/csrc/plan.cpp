@@ -123,20 +123,26 @@ int mid_splits(const TiledShape& t, int T, int N, int K) {
   return best;
 }
 
-// One range of K on 256-row tiles takes about K / 55 us (192 rows and fewer:
-// K / 64), the planes are written and read at about 4 TB/s, the pass adds 3
-// us. (A rank's share of the FFN: at 2 F = 7168, H = 8192 150 rows took 88 us
-// unsplit, 600 rows 113; at 14336, 400 rows 148.)
+// Times in us, fitted to 846 products of 129-2048 rows, N = 1024-32768 and K =
+// 512-8192 (within 10%, a few within 25%). Unsplit: one range of K on 128 x
+// 128 tiles, one per CU or two. Split: a range on 256-row tiles (192 rows and
+// fewer: skinny waves), the planes written and read, two launches' ends. What
+// saves less than 7% is left unsplit. (2 F = 7168: 150 rows, K = 8192 87 -> 36
+// us, K = 2048 26 -> 24 at best; 432 rows, K = 1024 16 -> 25.)
 int gate_up_splits(const TiledShape& t, int T) {
   const int N = 2 * t.ffn, K = t.hidden;
   if (N % 256 != 0) return 0;
   const long tiles = (long)(T + 255) / 256 * (N / 256);
-  const double range = T <= 192 ? K / 64.0 : K / 55.0;
+  const long tiles128 = (long)(T + 127) / 128 * (N / 128);
+  const double unsplit = tiles128 <= t.cus           ? 5 + K / 96.0
+                         : 2 * tiles128 <= 3 * t.cus ? 6 + K / 64.0
+                                                     : 6 + K / 57.0;
   int best = 0;
-  double cost = range;
+  double cost = 0.93 * unsplit;
   for (int sp = 2; sp <= kMaxMidSplits; sp *= 2) {
     if (tiles * sp > t.cus || K % (64 * sp) != 0 || (size_t)sp * T * N > t.gate_up_room) break;
-    const double c = range / sp + 2.0 * sp * T * N * 4 / 4e6 + 3;
+    const double range = (double)K / sp, plane = 1e-6 * sp * T * N;
+    const double c = T <= 192 ? 10 + range / 66 + 1.5 * plane : 10 + range / 58 + 1.2 * plane;
     if (c < cost) best = sp, cost = c;
   }
   return best;

@@ -148,6 +148,38 @@ void row_tail_check() {
   }
 }
 
+// Gate-up products of small steps: split over K where that is faster than one
+// range on 128 x 128 tiles, not where the planes and the second pass cost more
+// than they save (a short K, tiles that fill the CUs).
+void gate_up_check() {
+  auto splits = [](int T, int F, int K) { return gate_up_splits(shape(K, 64, 16, 128, F), T); };
+  struct { int T, N, K; } whole[] = {
+      {768, 2048, 1024}, {256, 1024, 1024}, {432, 3584, 1024}, {200, 7168, 1024}, {512, 7168, 2048},
+      {256, 14336, 2048}, {192, 16384, 2048}, {400, 2048, 512}, {1536, 2048, 2048},
+  };
+  for (auto c : whole) CHECK(splits(c.T, c.N / 2, c.K) == 0, "%d x %d K %d", c.T, c.N, c.K);
+  struct { int T, N, K, sp; } split[] = {
+      {150, 7168, 8192, 8}, {600, 7168, 8192, 2}, {400, 14336, 8192, 2}, {150, 14336, 8192, 4},
+      {200, 3584, 4096, 8}, {513, 512, 2048, 8},
+  };
+  for (auto c : split) {
+    const int sp = splits(c.T, c.N / 2, c.K);
+    CHECK(sp == c.sp, "%d x %d K %d: %d", c.T, c.N, c.K, sp);
+  }
+  for (int T = 129; T <= 2176; T += 61)
+    for (int F = 128; F <= 28672; F += 896)
+      for (int K = 512; K <= 8192; K *= 2) {
+        TiledShape t = shape(K, 64, 16, 128, F);
+        t.gate_up_room = (size_t)1 << 22;
+        const int sp = gate_up_splits(t, T);
+        CHECK(sp == 0 || sp == 2 || sp == 4 || sp == 8, "%d", sp);
+        if (sp == 0) continue;
+        CHECK(2 * F % 256 == 0 && K % (64 * sp) == 0, "tiles");
+        CHECK((size_t)sp * T * 2 * F <= t.gate_up_room, "room");
+        CHECK(up(T, 256) * (2 * F / 256) * sp <= t.cus, "one round");
+      }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -160,6 +192,8 @@ int main(int argc, char** argv) {
     half_round_check();
   else if (!std::strcmp(name, "row_tail"))
     row_tail_check();
+  else if (!std::strcmp(name, "gate_up"))
+    gate_up_check();
   else
     return 2;
   std::puts("ok");
