@@ -1476,15 +1476,12 @@ hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int
     const int m1 = M / 256 * 256;
     // A SwiGLU product's rows past the last multiple of 256 (at most 176 of
     // them) on the split-K kernel with one K range and SwiGLU in its
-    // epilogue: one more pass over the weights at ~6.3 TB/s, which costs
-    // about N / 78000 rounds of 256 x 256 tiles (~5.3 TFLOP/s per CU). Taken
+    // epilogue: one more pass over the weights (swiglu_tail_rounds). Taken
     // when that beats the tilings above, e.g. gate-up at 2048 + 128 rows:
     // -3% at N = 57344 (against the 128 x 128 tail below) and at N = 51200
     // (against 9 partly idle m-blocks), A/B on one box.
-    // 129..176 rows take an eighth longer.
-    const double tail = M - m1 <= 128 ? N / 78000.0 : N / 68000.0;
     if (epi == EPI_SWIGLU && m1 > 0 && m1 < M && M - m1 <= 176 && swiglu_tail_skinny() &&
-        cost_of(T256, m1) + tail < cost) {
+        cost_of(T256, m1) + swiglu_tail_rounds(M - m1, N, K) < cost) {
       const hipError_t e = launch(T256, 0, m1, 0, N);
       if (e != hipSuccess) return e;
       if (M - m1 > 128)

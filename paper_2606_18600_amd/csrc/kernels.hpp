@@ -195,6 +195,9 @@ hipError_t gemm_split_k(const void* A, const void* W, int M, int N, int K, int s
 // gemm: bf16 = LDS-tiled MFMA over packed A and W; fp32 = row-major, MFMA
 // tiles or, up to kGemvRows rows, one wave per output column.
 constexpr int kGemvRows = 8;
+// Cost of a SwiGLU product's last `rows` (at most 176) rows on the skinny
+// kernels, in rounds of 256 x 256 tiles, one per CU.
+double swiglu_tail_rounds(int rows, int N, int K);
 hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int N, int K,
                 void* out, hipStream_t s, RopeRows rope = RopeRows{});
 

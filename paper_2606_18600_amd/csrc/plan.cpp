@@ -148,6 +148,17 @@ int gate_up_splits(const TiledShape& t, int T) {
   return best;
 }
 
+double swiglu_tail_rounds(int rows, int N, int K) {
+  if (rows <= 128) return N / 78000.0;  // the weights at ~6.3 TB/s, a tile at ~5.3 TFLOP/s
+  // An eighth more at 144 rows and growing with the rows; fewer than ~190
+  // blocks of 256 columns no longer keep HBM busy, and the launch is one more
+  // (166 rows past 1024 at N = 16384, K = 2048: 76 us on two rounds of 192-row
+  // tiles, 91 so; 176 past 256 at 40960, 1024: 52 and 60; but past 512 at
+  // 40960, 8192 662 and 522).
+  const double pass = N / 68000.0 * (1 + (rows - 144) / 256.0);
+  return std::max(0.72, pass) + 100.0 / K;
+}
+
 int row_tail(const TiledShape& t, int T) {
   const int rt = T % 256, T0 = T - rt;
   if (rt == 0 || rt > t.tail_rows || T0 < 256) return 0;

@@ -180,6 +180,21 @@ void gate_up_check() {
       }
 }
 
+// 129-176 rows of SwiGLU past the last row of tiles: on the skinny kernel
+// where its pass is cheaper than the partial round it saves.
+void swiglu_tail_check() {
+  // rounds of 256-row tiles that the other tilings need less those that the
+  // whole rows of tiles need: 0.7 (two rounds of 192-row tiles), 0.9, 1
+  for (int K : {1024, 2048, 5120, 8192}) {
+    CHECK(swiglu_tail_rounds(166, 16384, K) > 0.7, "narrow, K %d", K);
+    CHECK(swiglu_tail_rounds(129, 34816, K) > 0.7, "K %d", K);
+    CHECK(swiglu_tail_rounds(176, 40960, K) < 0.9, "K %d", K);
+    CHECK(swiglu_tail_rounds(129, 57344, K) < 1 && swiglu_tail_rounds(144, 51200, K) < 1, "K %d", K);
+  }
+  CHECK(swiglu_tail_rounds(176, 57344, 1024) > 1 && swiglu_tail_rounds(176, 57344, 8192) < 1, "K");
+  CHECK(swiglu_tail_rounds(128, 57344, 8192) == 57344 / 78000.0, "up to 128 rows");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -194,6 +209,8 @@ int main(int argc, char** argv) {
     row_tail_check();
   else if (!std::strcmp(name, "gate_up"))
     gate_up_check();
+  else if (!std::strcmp(name, "swiglu_tail"))
+    swiglu_tail_check();
   else
     return 2;
   std::puts("ok");
