@@ -1352,12 +1352,12 @@ hipError_t gemm_split_k(const void* A, const void* W, int M, int N, int K, int s
                         hipStream_t s) {
   if (M == 0) return hipSuccess;
   if (splits < 1 || N % 256 != 0 || K % (64 * splits) != 0) return hipErrorInvalidValue;
-  if (M > 128 && M <= 192)
+  if (rows192_skinny(M, (long)(N / 256) * splits, K / splits))
     return launch_rows192<SK_PARTIAL>((const bf16_t*)A, (const bf16_t*)W, M, N, K, K / splits, out,
                                       s);
   dim3 grid((M + 255) / 256, N / 256, splits);
   // 192-row tiles where they take no more blocks (257..384 rows: [8192, 28672]
-  // in 4 ranges 160 us at 384 rows against 197)
+  // in 4 ranges 160 us at 384 rows against 197; up to 192 rows 5-10% less)
   if ((M + 191) / 192 == (int)grid.x) {
     launch_tiled<12, 4, 4, 2, EPI_STORE_F32>(grid, s, (const bf16_t*)A, (const bf16_t*)W, M, N, K,
                                              out, N, K / splits, (size_t)M * N, RopeRows{});
@@ -1412,8 +1412,11 @@ hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int
     return hipErrorInvalidValue;
   }
   if (N % 128 != 0 || K % 64 != 0) return hipErrorInvalidValue;
-  // One row tile of at most 176 rows whose 256-column blocks occupy most CUs.
-  if (epi == EPI_SWIGLU && M > 128 && M <= 176 && N >= 160 * 256 && N <= 256 * 256)
+  // One row tile of at most 176 rows whose 256-column blocks occupy most CUs
+  // (K = 512 at 176 rows, N = 40960: 20 us against 19 on tiles; from 1024 on it
+  // is 8-20% faster).
+  if (epi == EPI_SWIGLU && M <= 176 && N >= 160 * 256 && N <= 256 * 256 &&
+      rows192_skinny(M, N / 256, K))
     return launch_rows192<SK_SWIGLU>((const bf16_t*)A, (const bf16_t*)W, M, N, K, K, out, s);
   // Three tilings: 256 x 256 and 192 x 256 (8 waves, one block per CU) and
   // 128 x 128 (4 waves, two per CU). A product costs about its number of

@@ -187,9 +187,13 @@ int stream_fragments(int M, int N, int K, int splits, bool swiglu);
 int stream_splits(int N, int K, int max_splits, bool swiglu);
 hipError_t gemm_skinny(const void* A, const void* W, int M, int N, int K, int splits, bool swiglu,
                        void* out, hipStream_t s);
-// bf16 LDS-tiled product split over K: `splits` fp32 partial planes
-// [splits][M][N] (row stride N) of A [M, K] x W[N, K]^T, 256 x 256 tiles.
-// Needs N % 256 == 0 and K % (64 * splits) == 0.
+// bf16 product of more than 128 rows split over K: `splits` fp32 partial
+// planes [splits][M][N] (row stride N) of A [M, K] x W[N, K]^T, on tiles of 192
+// or 256 rows and 256 columns or (rows192_skinny) the eight-wave skinny
+// kernel. Needs N % 256 == 0 and K % (64 * splits) == 0.
+// Whether 129..192 rows in `blocks` blocks of 256 columns and k_len of K run
+// on the eight-wave skinny kernel rather than on 192-row tiles.
+bool rows192_skinny(int M, long blocks, int k_len);
 hipError_t gemm_split_k(const void* A, const void* W, int M, int N, int K, int splits, float* out,
                         hipStream_t s);
 // gemm: bf16 = LDS-tiled MFMA over packed A and W; fp32 = row-major, MFMA

@@ -99,6 +99,17 @@ PrefillParts prefill_split(int n_items, int n_kv, long long total, int longest, 
   return PrefillParts{};
 }
 
+// Product and consumer on 192-row tiles -> skinny, at 129 / 176 / 190 rows:
+// [2048, 3584] in 8 ranges 20 -> 20 / 21 -> 23 / 22 -> 24 us; [8192, 8192] in 8
+// (256 blocks) 45 -> 41 / 48 -> 45 / 50 -> 47; [2048, 8192] in 8 (64 blocks) 28
+// -> 27 / 30 -> 30 / 30 -> 32. A short range is over before the skinny waves'
+// reads ahead pay for their final sums, and 12 row tiles leave them no
+// registers to read ahead, which shows once a launch is not bound by HBM.
+bool rows192_skinny(int M, long blocks, int k_len) {
+  if (M <= 128 || M > 192 || k_len < 1024) return false;
+  return M <= 176 || blocks > 128;
+}
+
 size_t mid_capacity(int max_tokens, int N) {
   return std::max((size_t)kMidRows * N,
                   std::min(kMidElems, (size_t)kMaxMidSplits * max_tokens * N));

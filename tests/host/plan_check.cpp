@@ -195,6 +195,21 @@ void swiglu_tail_check() {
   CHECK(swiglu_tail_rounds(128, 57344, 8192) == 57344 / 78000.0, "up to 128 rows");
 }
 
+// 129-192 rows split over K: the skinny kernel for long K ranges only, and
+// past 176 rows for launches that fill most CUs only.
+void rows192_check() {
+  for (int blocks : {8, 64, 128, 256})
+    for (int k : {64, 128, 256, 512, 768})
+      for (int M : {129, 160, 176, 192}) CHECK(!rows192_skinny(M, blocks, k), "%d rows, %d", M, k);
+  for (int k : {1024, 2048, 3584, 8192}) {
+    for (int blocks : {8, 64, 128, 256})
+      for (int M : {129, 144, 160, 176}) CHECK(rows192_skinny(M, blocks, k), "%d rows, %d", M, k);
+    CHECK(rows192_skinny(191, 256, k) && rows192_skinny(177, 224, k), "most CUs");
+    CHECK(!rows192_skinny(191, 128, k) && !rows192_skinny(177, 64, k), "few CUs");
+    CHECK(!rows192_skinny(128, 256, k) && !rows192_skinny(193, 256, k), "rows");
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -211,6 +226,8 @@ int main(int argc, char** argv) {
     gate_up_check();
   else if (!std::strcmp(name, "swiglu_tail"))
     swiglu_tail_check();
+  else if (!std::strcmp(name, "rows192"))
+    rows192_check();
   else
     return 2;
   std::puts("ok");
