@@ -23,12 +23,14 @@ def _shape(name, hidden, nq, nkv, d, ffn):
 SPLIT = _shape("split", 2048, 8, 2, 128, 256)       # every product split, gate-up included
 HALF = _shape("half-round", 8192, 2, 1, 64, 128)    # 128 tiles of 256 x 256 at 769..1024 rows
 HALF_LONG = _shape("half-round-long-k", 8192, 2, 1, 64, 3584)  # ... and a K that is split there
+LONG = _shape("long-k", 4352, 2, 1, 64, 8192)      # K ranges of 1024 and more, 136 blocks
 WIDE = _shape("wide-ffn", 128, 2, 1, 64, 32768)     # 256 column tiles of gate-up
 
 
 @pytest.mark.parametrize("shape,rows", [
     (SPLIT, 129), (SPLIT, 192), (SPLIT, 193), (SPLIT, 257), (SPLIT, 385), (SPLIT, 513),
     (HALF, 769), (HALF, 1024), (HALF_LONG, 769),
+    (LONG, 129), (LONG, 160), (LONG, 161), (LONG, 192),
     (WIDE, 129), (WIDE, 176), (WIDE, 177), (WIDE, 257), (WIDE, 400), (WIDE, 432), (WIDE, 433),
 ], ids=lambda v: v.name if isinstance(v, synth.ModelShape) else str(v))
 def test_rows_around_the_turns(shape, rows):
