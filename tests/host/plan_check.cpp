@@ -155,7 +155,7 @@ void gate_up_check() {
   auto splits = [](int T, int F, int K) { return gate_up_splits(shape(K, 64, 16, 128, F), T); };
   struct { int T, N, K; } whole[] = {
       {768, 2048, 1024}, {256, 1024, 1024}, {432, 3584, 1024}, {200, 7168, 1024}, {512, 7168, 2048},
-      {256, 14336, 2048}, {192, 16384, 2048}, {400, 2048, 512}, {1536, 2048, 2048},
+      {256, 14336, 2048}, {192, 16384, 2048}, {400, 2048, 512}, {1536, 2048, 2048}, {1300, 3584, 3072},
   };
   for (auto c : whole) CHECK(splits(c.T, c.N / 2, c.K) == 0, "%d x %d K %d", c.T, c.N, c.K);
   struct { int T, N, K, sp; } split[] = {
