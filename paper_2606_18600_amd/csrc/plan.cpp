@@ -145,7 +145,7 @@ int gate_up_splits(const TiledShape& t, int T) {
   if (N % 256 != 0) return 0;
   const long tiles = (long)(T + 255) / 256 * (N / 256);
   const long tiles128 = (long)(T + 127) / 128 * (N / 128);
-  // (just past one per CU some of them still share a CU with nobody)
+  // (just past one per CU most of them still have a CU to themselves)
   const double unsplit = tiles128 <= t.cus           ? 5 + K / 96.0
                          : 4 * tiles128 <= 5 * t.cus ? 6 + K / 70.0
                          : 2 * tiles128 <= 3 * t.cus ? 6 + K / 62.0
