@@ -252,6 +252,20 @@ bool row_tail_for(const TiledShape& t, int T, int rt, int N);
 hipError_t attn_decode(DType dt, const void* q, KVLayer kv, SegTables tabs,
                        const DecodeItem* items, const int32_t* order, int n_items, int n_q,
                        float* part_o, float* part_ml, hipStream_t s);
+// Key splits of a step's decode sequences, at most: kMaxSplits or more, and
+// unless `even` in proportion to a sequence's key blocks.
+constexpr int kMaxSplits = 32;
+struct DecodeSplits {
+  int base = kMaxSplits;  // splits of a sequence of `mean` key blocks
+  long long mean = 1;
+  bool even = false;      // every sequence: base
+  int most(int nb) const {
+    const long long s = even ? base : base * (long long)nb / mean;
+    return s > kMaxSplits ? (int)s : kMaxSplits;
+  }
+};
+// For nd sequences with these cached tokens, n_kv heads of `group` query heads.
+DecodeSplits decode_splits(const int32_t* ctx_lens, int nd, int n_kv, int group, int cus);
 // Combines the partials of the tokens with several items (n_tok tokens in
 // all; those with a single item are left alone).
 hipError_t attn_merge(DType dt, const float* part_o, const float* part_ml,

@@ -99,6 +99,40 @@ PrefillParts prefill_split(int n_items, int n_kv, long long total, int longest, 
   return PrefillParts{};
 }
 
+// More splits shorten a long sequence's chain of keys but lengthen its merge,
+// one block per (token, kv head) that reads every split (kv1 x 16 heads, one
+// token of 60000 keys, us per layer: 32 splits 91, 64 72, 400 137; x 8 heads 82,
+// 60, 63). So with up to 12 (token, kv head) pairs sequences of ~14000 keys and
+// more get 64 each, of ~6400 48 (16 heads per group: 48 from 14000 on, up to 6
+// pairs); from 33 pairs on, where 32 splits each are 1.25 blocks per CU and
+// more, whatever evens out the waves (5 sequences of 60000 keys, 8 kv heads:
+// 246 -> 220). In between, 32 each; a longer sequence in proportion, if a block
+// per CU still holds them all (3 sequences of 18000-60000 keys, 8 kv heads: 127
+// -> 115; but 4 of 20000-40000, 256 blocks: 125 -> 153).
+DecodeSplits decode_splits(const int32_t* ctx_lens, int nd, int n_kv, int group, int cus) {
+  constexpr int kUnlimited = 1 << 20;
+  DecodeSplits r;
+  if (nd <= 0) return r;
+  long long total = 0;
+  for (int j = 0; j < nd; ++j) total += (ctx_lens[j] + kBlock) / kBlock;
+  r.mean = std::max(1LL, total / nd);
+  const long long pairs = (long long)nd * n_kv;
+  const bool wide = group > 8;
+  if (pairs <= (wide ? 6 : 12) && r.mean >= 900) {
+    r.base = wide ? 48 : 64;
+  } else if (pairs <= 8 && r.mean >= 400 && !wide) {
+    r.base = 48;
+  } else if (pairs > 32) {
+    r.even = true;
+    if (r.mean >= 500 && !wide) r.base = kUnlimited;
+  } else {
+    long long items = 0;
+    for (int j = 0; j < nd; ++j) items += r.most((ctx_lens[j] + kBlock) / kBlock);
+    r.even = items * ((n_kv + 3) / 4) > cus || (wide && r.mean < 900);
+  }
+  return r;
+}
+
 // Product and consumer on 192-row tiles -> skinny, at 129 / 176 / 190 rows:
 // [2048, 3584] in 8 ranges 20 -> 20 / 21 -> 23 / 22 -> 24 us; [8192, 8192] in 8
 // (256 blocks) 45 -> 41 / 48 -> 45 / 50 -> 47; [2048, 8192] in 8 (64 blocks) 28

@@ -42,7 +42,6 @@ stage_status fail(stage_status code, const char* fmt, ...) {
 }
 
 constexpr int kRing = 4;             // pinned staging buffers in flight
-constexpr int kMaxSplits = 32;       // decode key splits per sequence, at most
 constexpr int kSplitMinBlocks = 4;   // at least 4 blocks (64 keys) per split
 constexpr int kSplitNoneBlocks = 8;  // a step with no more blocks than this per token: no splits
 // A step of at most kWholePairs (token, kv head) pairs with at most this many
@@ -357,7 +356,7 @@ bool build_meta(const stage* st, const stage_batch* pf, const stage_batch* dc, i
   m.n_ditems = 0;
   // Key blocks per decode split: enough splits that the batch launches about
   // `attn_waves` waves (one round on the chip), at least kSplitMinBlocks
-  // blocks each, at most kMaxSplits splits per sequence.
+  // blocks each, as many per sequence as decode_splits allows.
   long long units = 0;
   int longest = 0;
   for (int j = 0; j < nd; ++j) {
@@ -375,10 +374,11 @@ bool build_meta(const stage* st, const stage_batch* pf, const stage_batch* dc, i
                       : longest <= kSplitNoneBlocks ? kSplitNoneBlocks
                                                     : kSplitMinBlocks;
   const int bps_target = (int)std::max<long long>(bps_min, (units + waves - 1) / waves);
-  // The workspace holds kMaxSplits splits per sequence of a small stage; a
-  // step of few sequences on a larger one may use the others' room (three
-  // sequences of 20000-65000 keys: 32 splits each 82 us, 67 each 76).
-  const int max_splits = std::max<int>(kMaxSplits, (int)(st->max_ditems / std::max(1, nd)));
+  // what the workspace holds: kMaxSplits splits per sequence of a small stage;
+  // a step of few sequences on a larger one may use the others' room
+  const int room = std::max<int>(kMaxSplits, (int)(st->max_ditems / std::max(1, nd)));
+  const DecodeSplits limit = decode_splits(nd ? dc->ctx_lens : nullptr, nd, st->cfg.n_kv_heads,
+                                           st->cfg.n_q_heads / st->cfg.n_kv_heads, st->cus);
   for (int j = 0; j < nd; ++j) {
     const int ctx = dc->ctx_lens[j];
     const int g = np + j;
@@ -390,7 +390,8 @@ bool build_meta(const stage* st, const stage_batch* pf, const stage_batch* dc, i
     if (st->cfg.dtype != STAGE_BF16) continue;  // fp32 attention needs no split plan
     const int keys = ctx + 1;
     const int nb = (keys + kBlock - 1) / kBlock;
-    int splits = std::min(max_splits, std::max(1, (nb + bps_target - 1) / bps_target));
+    int splits = std::max(1, (nb + bps_target - 1) / bps_target);
+    splits = std::min({splits, room, limit.most(nb)});
     const int bps = (nb + splits - 1) / splits;
     splits = (nb + bps - 1) / bps;
     if ((size_t)(m.n_ditems + splits) > st->max_ditems) return false;

@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <initializer_list>
+#include <vector>
 
 #include "../../paper_2606_18600_amd/csrc/kernels.hpp"
 
@@ -210,6 +211,38 @@ void rows192_check() {
   }
 }
 
+// Key splits of decode sequences: 32 each unless few long sequences gain by
+// more; never more for tokens whose merge would cost more than it saves.
+void decode_splits_check() {
+  auto most = [](std::initializer_list<int> ctx, int n_kv, int group, int j = 0) {
+    const DecodeSplits s = decode_splits(ctx.begin(), (int)ctx.size(), n_kv, group, 256);
+    return s.most((ctx.begin()[j] + kBlock) / kBlock);
+  };
+  for (int kv : {1, 2, 4}) {
+    CHECK(most({40000}, kv, 16) <= 64 && most({60000}, kv, 16) <= 64, "kv %d, 16 heads", kv);
+    CHECK(most({10000}, kv, 16) == 32, "kv %d, 16 heads, 10000 keys", kv);
+    CHECK(most({40000}, kv, 8) == 64 && most({10000}, kv, 8) == 48, "kv %d", kv);
+    CHECK(most({1000}, kv, 8) == 32, "kv %d, 1000 keys", kv);
+  }
+  CHECK(most({40000, 40000, 40000}, 8, 8) == 32, "24 pairs");
+  CHECK(most({60000, 20000, 40000}, 8, 8) == 47 && most({60000, 20000, 40000}, 8, 8, 1) == 32,
+        "24 uneven pairs");
+  CHECK(most({40000, 20000, 40000, 40000}, 8, 8) == 32, "a block per CU already");
+  CHECK(most({10000, 10000, 10000, 10000, 10000, 10000, 10000, 10000, 10000, 10000}, 1, 16) == 32,
+        "10 pairs of 16 heads");
+  CHECK(most({60000, 60000, 60000, 60000, 60000}, 8, 8) > 1000, "40 pairs: as the waves need");
+  for (int nd : {1, 3, 7, 64, 200}) {  // any step: a positive count for every sequence
+    std::vector<int32_t> ctx(nd);
+    for (int j = 0; j < nd; ++j) ctx[j] = j * 7919 % 65000;
+    for (int kv : {1, 3, 8, 32})
+      for (int g : {1, 16}) {
+        const DecodeSplits s = decode_splits(ctx.data(), nd, kv, g, 256);
+        for (int c : ctx) CHECK(s.most((c + kBlock) / kBlock) >= kMaxSplits, "nd %d", nd);
+      }
+  }
+  CHECK(decode_splits(nullptr, 0, 8, 8, 256).most(1) == kMaxSplits, "no sequence");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -228,6 +261,8 @@ int main(int argc, char** argv) {
     swiglu_tail_check();
   else if (!std::strcmp(name, "rows192"))
     rows192_check();
+  else if (!std::strcmp(name, "decode_splits"))
+    decode_splits_check();
   else
     return 2;
   std::puts("ok");

@@ -24,7 +24,8 @@ def _shape(nq, nkv, d):
 
 @pytest.mark.parametrize("nq,nkv,d,seqs,longest", [
     (8, 1, 128, 3, 1500),    # 8 waves per token, up to 24 splits
-    (8, 1, 128, 1, 6000),    # one token, 94 splits
+    (8, 1, 128, 1, 6000),    # one token, 32 splits
+    (8, 1, 128, 1, 8000),    # one token, 48 splits
     (16, 1, 128, 5, 900),    # group 16: 4 waves
     (4, 4, 64, 32, 1100),    # 128 (token, kv head) pairs: 8 waves
     (8, 4, 64, 33, 1100),    # 132: 4 waves

@@ -28,7 +28,7 @@ def exe(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["prefill_parts", "stream", "half_round", "row_tail", "gate_up",
-                                   "swiglu_tail", "rows192"])
+                                   "swiglu_tail", "rows192", "decode_splits"])
 def test_sizing_rules(exe, check):
     r = subprocess.run([exe, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stderr[-2000:]
