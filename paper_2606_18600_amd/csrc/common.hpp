@@ -9,6 +9,8 @@ typedef uint16_t bf16_t;  // bfloat16 bits in memory
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+// fp32 values of the caller (weights, KV pool), at any multiple of 4 bytes
+typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));

@@ -893,8 +893,8 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(
     const float* kp = kv + ((size_t)id * n_kv + kvh) * 2 * plane + lane * 8;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      kn[j][0] = *(const f32x4_t*)(kp + j * 512);
-      kn[j][1] = *(const f32x4_t*)(kp + j * 512 + 4);
+      kn[j][0] = *(const f32x4_any_t*)(kp + j * 512);
+      kn[j][1] = *(const f32x4_any_t*)(kp + j * 512 + 4);
     }
     vn = kp + plane;
   };
@@ -908,8 +908,8 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(
     vp = vn;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      vf[j][0] = *(const f32x4_t*)(vp + j * 512);
-      vf[j][1] = *(const f32x4_t*)(vp + j * 512 + 4);
+      vf[j][0] = *(const f32x4_any_t*)(vp + j * 512);
+      vf[j][1] = *(const f32x4_any_t*)(vp + j * 512 + 4);
     }
     if (b + NW < nb) load(b + NW);
     // two chains of products, so that one's latency hides behind the other

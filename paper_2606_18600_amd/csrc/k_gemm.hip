@@ -995,9 +995,6 @@ template <> struct f32_tile<16> {
   __device__ static __forceinline__ acc mul(float a, float b, acc c) { return mfma16x16x4(a, b, c); }
 };
 
-// the caller's fp32 weights may lie at any multiple of 4 bytes
-typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
-
 template <int S, int RT, int CT, int WM, int WN, int KS, int KC, int EPI>
 __global__ __launch_bounds__(WM * WN * KS * 64) void gemm_f32(const float* __restrict__ A,
                                                               const float* __restrict__ W, int M,

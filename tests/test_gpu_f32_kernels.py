@@ -1,6 +1,8 @@
 """The fp32 mode's matrix-core kernels at the sizes where their dispatch
-turns: GEMM tiles of 128, 64, 32 and 16 (through the LM head, whose vocabulary and row count are free in the fp32 mode), and
-attention blocks that hold tokens of several sequences."""
+turns: GEMM tiles of 128, 64, 32 and 16 (the plain store through the LM head,
+whose vocabulary and row count are free in the fp32 mode; SwiGLU and residual
+add through layers), attention blocks that hold tokens of several sequences,
+and buffers that are aligned to 4 bytes only."""
 
 from __future__ import annotations
 
@@ -109,3 +111,70 @@ def test_other_requests_and_unwritten_slots_stay_out(shape):
     assert torch.equal(out["plain"], out["nan pool"])
     keep = [0, 1, 2, *range(9, 28)]
     assert torch.equal(out["plain"][keep], out["nan rows"][keep])
+
+
+WIDE_FFN = synth.ModelShape("wide-ffn", hidden=256, n_q_heads=4, n_kv_heads=2, head_dim=64,
+                            ffn=8256, rms_eps=1e-5, rope_theta=1e4)
+WIDE_HIDDEN = synth.ModelShape("wide-hidden", hidden=8192, n_q_heads=2, n_kv_heads=1, head_dim=64,
+                               ffn=192, rms_eps=1e-5, rope_theta=1e4)
+
+
+@pytest.mark.parametrize("shape,rows", [
+    (WIDE_FFN, 100), (WIDE_FFN, 128),        # SwiGLU on 64-row tiles: 129 columns of them
+    (WIDE_FFN, 129), (WIDE_FFN, 300),        # ... on 128-row tiles
+    (WIDE_HIDDEN, 129), (WIDE_HIDDEN, 383),  # residual add on 64 x 64 tiles
+    (WIDE_HIDDEN, 450),                      # ... on 128 x 128 tiles
+], ids=lambda v: v.name if isinstance(v, synth.ModelShape) else str(v))
+def test_layer_tiles(shape, rows):
+    """One layer against the exact oracle, output, branch and each row's
+    branch: fp32 sums of at most 8256 terms of random sign, about 1e-6 as in
+    the other layers here; a misplaced row or column moves a row by tens of
+    percent."""
+    seed = rows
+    pair = Pair(shape, "f32", 1, 40, 512, 4, seed, host_weights=[strong_weights(shape, seed, 0)])
+    lens = np.array([rows], np.int32)
+    bt = synth.make_block_tables(lens, 40, synth.BlockAllocator(40, seed))
+    try:
+        y, yr, x = pair.prefill(lens, np.zeros(1, np.int32), bt,
+                                synth.hidden_states(seed, 1, rows, shape.hidden))
+        e, worst = rel_l2(y - x, yr - x), max(rel_l2(a, b) for a, b in zip(y - x, yr - x))
+        log(f"{shape.name} rows={rows}: branch {e:.2e} worst row {worst:.2e}")
+        assert rel_l2(y, yr) <= 1e-5 and e <= 1e-5 and worst <= 1e-4
+    finally:
+        pair.close()
+
+
+def _shifted(t):
+    """A copy of t that starts 4 bytes past a 16-byte multiple."""
+    flat = torch.empty(t.numel() + 4, dtype=t.dtype, device="cuda")[1:1 + t.numel()]
+    assert flat.data_ptr() % 16 == 4
+    return flat.view(t.shape).copy_(t)
+
+
+@pytest.mark.parametrize("shape", [G1, G2], ids=lambda s: s.name)
+def test_buffers_aligned_to_four_bytes(shape):
+    """Weights, KV pool and hidden rows may lie at any multiple of 4 bytes in
+    the fp32 mode: a prefill and a decode give the same bits there."""
+    seed = 7
+    lens = np.array([3, 37], np.int32)
+    bt = torch.from_numpy(synth.make_block_tables(lens + 1, 3, synth.BlockAllocator(8, seed))).cuda()
+    x = torch.from_numpy(synth.hidden_states(seed, 1, 40, shape.hidden)).cuda()
+    xd = torch.from_numpy(synth.hidden_states(seed, 2, 2, shape.hidden)).cuda()
+    host = [{k: v.astype(np.float32) for k, v in strong_weights(shape, seed, l).items()}
+            for l in range(2)]
+    out = []
+    for place in (lambda t: t, _shifted):
+        w = [{k: place(v) for k, v in upload_weights(h, "f32").items()} for h in host]
+        pool = place(torch.zeros(2 * 8 * shape.n_kv_heads * 2 * 16 * shape.head_dim, device="cuda"))
+        # (fp32 weights are stored row-major: packing them is a copy)
+        st = DeviceStage(shape, "f32", 0, w, 8, 64, 4, kv_pool=pool, packed=True)
+        try:
+            y = st.prefill(lens, [0, 0], bt, place(x), place(torch.empty_like(x)))
+            yd = st.decode(lens, bt, place(xd), place(torch.empty_like(xd)))
+            torch.cuda.synchronize()
+            out.append((y.clone(), yd.clone(), pool.clone()))
+        finally:
+            st.close()
+    assert torch.isfinite(out[0][0]).all() and torch.isfinite(out[0][1]).all()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
