@@ -263,7 +263,9 @@ void plan_workspace(stage* st) {
   take(st->r_q, T * qw * es);
   take(st->r_attn, Tp * qw * es);
   take(st->r_m, Tp * F * es);
-  const size_t gu_rows = c.dtype == STAGE_F32 ? T : (st->s_gu > 1 ? (size_t)st->s_gu * R : 0);
+  // gate and up columns: fp32 steps of at most kGemvRows rows, split-K planes
+  const size_t gu_rows = c.dtype == STAGE_F32 ? std::min<size_t>(T, kGemvRows)
+                                              : (st->s_gu > 1 ? (size_t)st->s_gu * R : 0);
   take(st->r_gu, gu_rows * 2 * F * 4);
   // split-K planes of the O / down products of skinny steps and of the last
   // rows of a large step, the mid-split planes, and the QKV planes of the

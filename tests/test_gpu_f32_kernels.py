@@ -178,3 +178,15 @@ def test_buffers_aligned_to_four_bytes(shape):
     assert torch.isfinite(out[0][0]).all() and torch.isfinite(out[0][1]).all()
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+def test_workspace_without_unused_planes():
+    """Only steps of at most 8 rows keep the gate and up columns in memory."""
+    shape = synth.ModelShape("f", hidden=128, n_q_heads=2, n_kv_heads=2, head_dim=64, ffn=16384,
+                             rms_eps=1e-5, rope_theta=1e4)
+    st = DeviceStage(shape, "f32", 0, [upload_weights(synth.host_layer_weights(shape, 1, 0), "f32")],
+                     4, 1024, 4, max_position=64)
+    try:
+        assert st.workspace.numel() < 1.1 * 1024 * (shape.ffn + 8 * shape.hidden) * 4
+    finally:
+        st.close()
