@@ -11,14 +11,18 @@
 //   Every operand is one contiguous fragment load. The C layout of the first
 //   product (lane l: row l%16, keys (l/16)*4 + r) is exactly the B layout
 //   the second needs, and each lane keeps the online softmax statistics of
-//   its own row (4-lane row reductions). Partial (max, sum, unnormalised
-//   output) go to a workspace, and attn_merge_kernel combines the splits.
+//   its own row (4-lane row reductions). A token's only split writes the
+//   finished row; several splits leave (max, sum, unnormalised output) in a
+//   workspace, and attn_merge_kernel combines them.
+// * attn_decode_item_bf16: the same products, one 8-wave workgroup per (decode
+//   token, kv head): the waves share the token's keys and combine in LDS.
 // * attn_prefill_bf16: one 4-wave workgroup per (128 rows of a chunk, kv
 //   head); rows are (position, head) pairs of the chunk, keys run from 0 to
 //   the last position of the chunk (the chunk's own keys are already in the
 //   cache), with the causal mask applied per row. Both products on
 //   v_mfma_f32_32x32x16_bf16, with operands gathered per lane from the same
-//   fragments (staged in LDS).
+//   fragments (staged in LDS). Few, long chunks share an item's keys between
+//   several workgroups, whose parts attn_prefill_merge combines.
 // * attn_f32_kernel: the fp32 mode, prefill and decode rows alike: one
 //   workgroup per (up to 16 (token, head) rows, kv head) on fp32 MFMA.
 #include <type_traits>

@@ -1195,7 +1195,8 @@ bool skinny_rot() {
   return on;
 }
 
-// 65..128 rows run on the 8-wave kernel unless STAGE_SKINNY8=0 (read once).
+// 65..128 rows run on the 8-wave kernel unless STAGE_SKINNY8=0 (read once);
+// 129..192 rows (launch_rows192) have no other skinny kernel.
 bool skinny8_enabled() {
   static const bool on = [] {
     const char* v = getenv("STAGE_SKINNY8");
@@ -1224,12 +1225,15 @@ hipError_t launch_skinny_kp(const bf16_t* a, const bf16_t* w, int M, int N, int 
                             int splits, bool swiglu, void* out, hipStream_t s) {
   const int groups = N / 64;
   dim3 grid((groups + kSkinnyKpGroups - 1) / kSkinnyKpGroups, splits);
-  if (swiglu)
-    gemm_skinny_kp_bf16<MT, kSkinnyKpGroups, SK_SWIGLU>
-        <<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len, out, skinny_rot());
-  else
+  if (!swiglu) {
     gemm_skinny_kp_bf16<MT, kSkinnyKpGroups, SK_PARTIAL>
         <<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len, out, skinny_rot());
+  } else if constexpr (MT > 1) {
+    gemm_skinny_kp_bf16<MT, kSkinnyKpGroups, SK_SWIGLU>
+        <<<grid, 512, 0, s>>>(a, w, M, N, K, kb_len, out, skinny_rot());
+  } else {
+    return hipErrorInvalidValue;  // the stream kernel takes every such product
+  }
   return hipGetLastError();
 }
 
@@ -1282,10 +1286,10 @@ hipError_t gemm_skinny(const void* A, const void* W, int M, int N, int K, int sp
     if (M <= 16) return launch_stream<1>(a, w, M, N, K, kb, splits, frags == 2, swiglu, out, s);
     return launch_stream<2>(a, w, M, N, K, kb, splits, frags == 2, swiglu, out, s);
   }
-  // A SwiGLU product whose groups, four to a block, leave a third of the CUs
-  // without one (a rank's half of a wide FFN) runs two groups to a block:
+  // A SwiGLU product whose groups, four to a block, leave half of the CUs or
+  // more without one (a rank's half of a wide FFN) runs two groups to a block:
   // a three-layer decode step of 64 rows at N = 28672, K = 8192 went from 738
-  // to 625 us with it, of 4 rows from 593 to 538 us.
+  // to 625 us with it. (One row tile of that width is on the stream kernel.)
   if (skinny_kp_used(K, splits, swiglu) ||
       (swiglu && N / 64 <= 512 && K % 128 == 0 && skinny_kp_enabled())) {
     switch ((M + 15) / 16) {

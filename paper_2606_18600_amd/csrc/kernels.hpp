@@ -159,7 +159,8 @@ int skinny_kb_len(int K, int splits);
 // k-part kernel: 8 waves on kSkinnyKpGroups weight groups, K ranges a
 // multiple of 128, so a launch has half the K ranges of the four-group
 // kernels for the same number of blocks. STAGE_SKINNY_KP=0 turns it off
-// (read once).
+// (read once). Products of at most kStreamRows rows may run on
+// gemm_stream_bf16 instead, which has no switch.
 constexpr int kSkinnyKpGroups = 2;
 bool skinny_kp_enabled();
 bool skinny_kp_used(int K, int splits, bool swiglu);
