@@ -187,6 +187,10 @@ def test_workspace_without_unused_planes():
     st = DeviceStage(shape, "f32", 0, [upload_weights(synth.host_layer_weights(shape, 1, 0), "f32")],
                      4, 1024, 4, max_position=64)
     try:
-        assert st.workspace.numel() < 1.1 * 1024 * (shape.ffn + 8 * shape.hidden) * 4
+        # the FFN activations, padded to whole 192-row tiles (1152 rows), the
+        # gate and up columns of 8 rows, and room for 8 regions as wide as the
+        # residual: 81 MB (the gate and up columns of every row: 134 MB more)
+        limit = 4 * 1152 * (shape.ffn + 8 * shape.hidden) + 4 * 8 * 2 * shape.ffn
+        assert st.workspace.numel() < limit
     finally:
         st.close()
