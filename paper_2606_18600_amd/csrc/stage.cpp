@@ -641,6 +641,7 @@ stage_status run_step(stage* st, const stage_batch* pf, const stage_batch* dc, c
       KVLayer kvl{st->kv_pool + (size_t)li * st->kv_layer_bytes, nkv, D};
       if (li > 0)
         L(STAGE_OP_NORM, [&] { return rmsnorm(dt, x, pending, h, w.attn_norm, T, H, c.rms_eps, ls); });
+      pending = Partials{nullptr, 0};  // (O may leave none of its own)
 
       // where RoPE finds the projection: [T][qkvw], possibly in split planes,
       // or the query columns [T][qw] and split planes of the key/value columns
