@@ -449,8 +449,10 @@ hipError_t embed_norm(DType dt, const void* hidden_in, float* x, void* h, const 
   if (T == 0) return hipSuccess;
   const Partials none{nullptr, 0};
   // Eight rows per block for wide rows (2048 x 8192 44.5 us with one row per
-  // block, 33.0 so; 2176 x 5120 29.9 against 32.9). Its 16-byte loads need the
-  // caller's rows and gain aligned, which may lie at any multiple of 8.
+  // block, 33.0 so; at 7168 12 us less too, and 2-4 less at 1024 or 2176 rows
+  // of either width; at 5120 and 6144 7-11 less at 2048 rows, nothing at 1024,
+  // and 2176 x 5120 29.9 against 32.9). Its 16-byte loads need the caller's
+  // rows and gain aligned, which may lie at any multiple of 8.
   if (dt == DT_BF16 && T >= 1024 && H % 1024 == 0 && H > 6144 && H <= 8192 &&
       ((uintptr_t)hidden_in | (uintptr_t)gain) % 16 == 0) {
     rmsnorm_rows8_kernel<true><<<(T + 7) / 8, 1024, 0, s>>>((const bf16_t*)hidden_in, rows, x, T, H,
