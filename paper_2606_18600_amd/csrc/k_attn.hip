@@ -1130,7 +1130,7 @@ hipError_t attn_f32(const float* q, KVLayer kv, SegTables tabs, const int32_t* t
   // whole 16-row tiles, unless that leaves more than half of the CUs without
   // a block: then fewer tokens (and more padding rows) per block
   int P = 16 / (n_q / kv.n_kv);
-  while (P > 1 && (long)((n_tok + P - 1) / P) * kv.n_kv < 128) P /= 2;
+  while (P > 1 && (long)((n_tok + P - 1) / P) * kv.n_kv < kCus / 2) P /= 2;
   dim3 grid((n_tok + P - 1) / P, kv.n_kv, P);
   if (kv.head_dim == 128)
     attn_f32_kernel<128><<<grid, kF32Waves * 64, 0, s>>>(q, (const float*)kv.base, kv.n_kv, tabs,

@@ -1121,11 +1121,11 @@ hipError_t launch_gemm_f32(const float* A, const float* W, int M, int N, int K, 
   auto up = [](int v, int t) { return (v + t - 1) / t; };
   auto tiles = [&](int tm, int tn) { return (long)up(M, tm) * up(cols, tn); };
   constexpr int BN = kSwiglu ? 64 : 128;  // columns of the largest tile
-  if (tiles(128, BN) >= 256)
+  if (tiles(128, BN) >= kCus)
     gemm_f32<32, 2, 2, 2, 2, 1, 16, EPI><<<dim3(up(M, 128), up(cols, BN)), 256, 0, s>>>(A, W, M, N, K, out);
-  else if (tiles(64, 64) >= 256)
+  else if (tiles(64, 64) >= kCus)
     gemm_f32<32, 1, CT, 2, 2, 2, 32, EPI><<<dim3(up(M, 64), up(cols, 64)), 512, 0, s>>>(A, W, M, N, K, out);
-  else if (tiles(32, 32) > 128)
+  else if (tiles(32, 32) > kCus / 2)
     gemm_f32<32, 1, CT, 1, 1, 4, 16, EPI><<<dim3(up(M, 32), up(cols, 32)), 256, 0, s>>>(A, W, M, N, K, out);
   else
     gemm_f32<16, 1, CT, 1, 1, 4, 16, EPI><<<dim3(up(M, 16), up(cols, 16)), 256, 0, s>>>(A, W, M, N, K, out);
@@ -1416,7 +1416,7 @@ hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int
   // One row tile of at most 176 rows whose 256-column blocks occupy most CUs
   // (K = 512 at 176 rows, N = 40960: 20 us against 19 on tiles; from 1024 on it
   // is 8-20% faster).
-  if (epi == EPI_SWIGLU && M <= 176 && N >= 160 * 256 && N <= 256 * 256 &&
+  if (epi == EPI_SWIGLU && M <= 176 && N >= kCus * 5 / 8 * 256 && N <= kCus * 256 &&
       rows192_skinny(M, N / 256, K))
     return launch_rows192<SK_SWIGLU>((const bf16_t*)A, (const bf16_t*)W, M, N, K, K, out, s);
   // Three tilings: 256 x 256 and 192 x 256 (8 waves, one block per CU) and

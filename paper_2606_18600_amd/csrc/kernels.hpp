@@ -12,6 +12,10 @@ enum DType { DT_F32 = 0, DT_BF16 = 1 };
 
 // GEMM epilogues. The GEMM computes acc[m][n] = sum_k A[m][k] * W[n][k]
 // (A row-major [M,K], W row-major [N,K]).
+// CUs of an unpartitioned MI355X, which the launchers' rules count with (the
+// stage's own rules take the device's number).
+constexpr int kCus = 256;
+
 enum Epilogue {
   EPI_STORE_F32 = 0,  // out (fp32, [M, N]) = acc
   EPI_RESID_ADD = 1,  // out (fp32 residual, [M, N]) += acc
@@ -182,27 +186,27 @@ int skinny_kp_splits(int N, int K, int target_blocks, int max_splits = kSkinnyMa
 // a reduction of 5; [7168, 8192] in halves 21.1 against 20.3 and 4.6; and up
 // to 16 rows it takes two blocks per CU ([28672, 8192] 72.3 us against 74.4).
 constexpr int kStreamRows = 32;
-constexpr int kStreamBlocks = 256;
+constexpr int kStreamBlocks = kCus;
 constexpr int kStreamMaxRange = 4096;
 int stream_fragments(int M, int N, int K, int splits, bool swiglu);
 int stream_splits(int N, int K, int max_splits, bool swiglu);
 hipError_t gemm_skinny(const void* A, const void* W, int M, int N, int K, int splits, bool swiglu,
                        void* out, hipStream_t s);
+// Whether 129..192 rows in `blocks` blocks of 256 columns and k_len of K run
+// on the eight-wave skinny kernel rather than on 192-row tiles.
+bool rows192_skinny(int M, long blocks, int k_len);
 // bf16 product of more than 128 rows split over K: `splits` fp32 partial
 // planes [splits][M][N] (row stride N) of A [M, K] x W[N, K]^T, on tiles of 192
 // or 256 rows and 256 columns or (rows192_skinny) the eight-wave skinny
 // kernel. Needs N % 256 == 0 and K % (64 * splits) == 0.
-// Whether 129..192 rows in `blocks` blocks of 256 columns and k_len of K run
-// on the eight-wave skinny kernel rather than on 192-row tiles.
-bool rows192_skinny(int M, long blocks, int k_len);
 hipError_t gemm_split_k(const void* A, const void* W, int M, int N, int K, int splits, float* out,
                         hipStream_t s);
-// gemm: bf16 = LDS-tiled MFMA over packed A and W; fp32 = row-major, MFMA
-// tiles or, up to kGemvRows rows, one wave per output column.
-constexpr int kGemvRows = 8;
 // Cost of a SwiGLU product's last `rows` (at most 176) rows on the skinny
 // kernels, in rounds of 256 x 256 tiles, one per CU.
 double swiglu_tail_rounds(int rows, int N, int K);
+// gemm: bf16 = LDS-tiled MFMA over packed A and W; fp32 = row-major, MFMA
+// tiles or, up to kGemvRows rows, one wave per output column.
+constexpr int kGemvRows = 8;
 hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int N, int K,
                 void* out, hipStream_t s, RopeRows rope = RopeRows{});
 

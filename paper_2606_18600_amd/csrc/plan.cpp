@@ -83,8 +83,10 @@ PrefillParts prefill_split(int n_items, int n_kv, long long total, int longest, 
   // stages, and only where that pays: a stage takes about 1.3 us with a block
   // per CU and 2.4 with two, the combining pass 10 (400 rows behind 1000 keys
   // gain nothing; 150 rows and one kv head behind 700, 10 stages' chain less
-  // on a nearly empty chip, 14 us per layer).
-  constexpr int kBlocks = 512, kMinStages = 4;
+  // on a nearly empty chip, 14 us per layer). At head_dim 64 as well: of 110
+  // random steps of 1-16 heads per group and 150-6000 cached keys none is
+  // slower than unsplit beyond noise, those of 500 keys and more 4-40% faster.
+  constexpr int kBlocks = 2 * kCus, kMinStages = 4;
   const long long blocks = (long long)n_items * n_kv;
   if (blocks >= kBlocks) return PrefillParts{};
   long long stages = std::max<long long>(kMinStages, (total * n_kv + kBlocks - 1) / kBlocks);

@@ -51,9 +51,9 @@ constexpr int kSplitNoneBlocks = 8;  // a step with no more blocks than this per
 // per layer: 16 pairs of 19 blocks 2.5 us less, 16 pairs of 63 blocks 3.3 us
 // more, 128 pairs of up to 63 blocks 6 us less; 400 pairs of them 2.5 us less
 // on the 32B shape).
-constexpr int kWholePairs = 512;
+constexpr int kWholePairs = 2 * kCus;
 int whole_blocks(long long pairs) {
-  return pairs > kWholePairs ? 0 : pairs >= 128 ? 64 : 32;
+  return pairs > kWholePairs ? 0 : pairs >= kCus / 2 ? 64 : 32;
 }
 constexpr int kSkinnyMaxRows = 128;  // decode-sized steps use split-K GEMMs
 constexpr int kMaxKvSplits = 4;      // K splits of the key/value columns of a prefill QKV
