@@ -1416,7 +1416,7 @@ hipError_t gemm(DType dt, Epilogue epi, const void* A, const void* W, int M, int
   // One row tile of at most 176 rows whose 256-column blocks occupy most CUs
   // (K = 512 at 176 rows, N = 40960: 20 us against 19 on tiles; from 1024 on it
   // is 8-20% faster).
-  if (epi == EPI_SWIGLU && M <= 176 && N >= kCus * 5 / 8 * 256 && N <= kCus * 256 &&
+  if (epi == EPI_SWIGLU && M <= 176 && K >= 1024 && N >= kCus * 5 / 8 * 256 && N <= kCus * 256 &&
       rows192_skinny(M, N / 256, K))
     return launch_rows192<SK_SWIGLU>((const bf16_t*)A, (const bf16_t*)W, M, N, K, K, out, s);
   // Three tilings: 256 x 256 and 192 x 256 (8 waves, one block per CU) and

@@ -138,11 +138,24 @@ DecodeSplits decode_splits(const int32_t* ctx_lens, int nd, int n_kv, int group,
 // Product and consumer on 192-row tiles -> skinny, at 129 / 176 / 190 rows:
 // [2048, 3584] in 8 ranges 20 -> 20 / 21 -> 23 / 22 -> 24 us; [8192, 8192] in 8
 // (256 blocks) 45 -> 41 / 48 -> 45 / 50 -> 47; [2048, 8192] in 8 (64 blocks) 28
-// -> 27 / 30 -> 30 / 30 -> 32. A short range is over before the skinny waves'
-// reads ahead pay for their final sums, and 12 row tiles leave them no
-// registers to read ahead, which shows once a launch is not bound by HBM.
+// -> 27 / 30 -> 30 / 30 -> 32. 12 row tiles leave the skinny waves no registers
+// to read ahead, which shows once a launch is not bound by HBM. Ranges below
+// 1024 are over before their reads ahead pay for their final sums, but with
+// most CUs at work the kernels around a tiled product lose more (two norms, RoPE
+// and attention 2-3 us in all): whole layers of O and down in 8 ranges, tiles
+// -> skinny at 130 / 160 / 190 rows, N = 4096 (128 blocks) and ranges of 768
+// 108 -> 114 / 112 -> 118 / 119 -> 128 us, 5120 122 -> 125 / 128 -> 131 / 138 ->
+// 143, 6144 136 -> 134 / 143 -> 143 / 154 -> 156, 7168 151 -> 146 / 160 -> 157 /
+// 170 -> 171, 8192 164 -> 159 / 174 -> 170 / 186 -> 186 (one rank of 4, ranges
+// of 896, 8192: 177 -> 172 / 187 -> 182 / 200 -> 197). With few blocks the
+// final sums are short, and ranges from 640 on pay for them up to 160 rows (32
+// to 96 blocks, ranges of 768, product alone at 129 / 160 / 176 / 190 rows 18.3
+// -> 17.3 / 18.7 -> 18.4 / 19.0 -> 19.3 / 19.4 -> 21.2).
 bool rows192_skinny(int M, long blocks, int k_len) {
-  if (M <= 128 || M > 192 || k_len < 1024) return false;
+  if (M <= 128 || M > 192) return false;
+  if (k_len < 1024)
+    return 8 * blocks > (M <= 176 ? 5 : 7) * kCus ||
+           (k_len >= 640 && M <= 160 && 8 * blocks <= 3 * kCus);
   return M <= 176 || blocks > 128;
 }
 

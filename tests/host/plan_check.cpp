@@ -196,12 +196,20 @@ void swiglu_tail_check() {
   CHECK(swiglu_tail_rounds(128, 57344, 8192) == 57344 / 78000.0, "up to 128 rows");
 }
 
-// 129-192 rows split over K: the skinny kernel for long K ranges only, and
-// past 176 rows for launches that fill most CUs only.
+// 129-192 rows split over K: the skinny kernel for long K ranges, and for
+// short ranges and past 176 rows where the launch fills most CUs.
 void rows192_check() {
-  for (int blocks : {8, 64, 128, 256})
-    for (int k : {64, 128, 256, 512, 768})
-      for (int M : {129, 160, 176, 192}) CHECK(!rows192_skinny(M, blocks, k), "%d rows, %d", M, k);
+  for (int k : {64, 128, 256, 448, 512, 768, 896}) {
+    for (int M : {129, 160, 176, 192}) {
+      for (int blocks : {112, 128, 160}) CHECK(!rows192_skinny(M, blocks, k), "%d rows, %d", M, k);
+      for (int blocks : {8, 64, 96})
+        CHECK(rows192_skinny(M, blocks, k) == (k >= 640 && M <= 160), "%d rows, %d", M, k);
+    }
+    for (int M : {129, 144, 160, 176})
+      CHECK(rows192_skinny(M, 192, k) && rows192_skinny(M, 256, k), "%d rows, %d", M, k);
+    CHECK(!rows192_skinny(190, 192, k) && !rows192_skinny(190, 224, k), "190 rows, %d", k);
+    CHECK(rows192_skinny(190, 256, k), "190 rows of 256 blocks, %d", k);
+  }
   for (int k : {1024, 2048, 3584, 8192}) {
     for (int blocks : {8, 64, 128, 256})
       for (int M : {129, 144, 160, 176}) CHECK(rows192_skinny(M, blocks, k), "%d rows, %d", M, k);
