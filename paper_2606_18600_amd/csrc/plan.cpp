@@ -185,10 +185,14 @@ int mid_splits(const TiledShape& t, int T, int N, int K) {
 
 // Times in us, fitted to 846 products of 129-2048 rows, N = 1024-32768 and K =
 // 512-8192 (within 10%, a few within 25%). Unsplit: one range of K on 128 x
-// 128 tiles, one per CU or two. Split: a range on 256-row tiles (192 rows and
-// fewer: skinny waves), the planes written and read, two launches' ends. What
-// saves less than 7% is left unsplit. (2 F = 7168: 150 rows, K = 8192 87 -> 36
-// us, K = 2048 26 -> 24 at best; 432 rows, K = 1024 16 -> 25.)
+// 128 tiles, one per CU or two. Split: a range on 256-row tiles, the planes
+// written and read, two launches' ends; for 192 rows and fewer fitted to what
+// 264 whole layers take with each number of ranges, since there the kernels
+// around the product gain as well. What saves less than 7% is left unsplit.
+// Layers are 0.1 us from their best choice on average up to 192 rows (3 at
+// most), 0.3 of 245 layers of 224-900 rows (7). (2 F = 7168: 150 rows, K = 8192
+// 87 -> 36 us, but 432 rows, K = 1024 16 -> 25; 2 F = 14336, 130 rows, K =
+// 2560: layer of 101 us unsplit, 98 in 2 ranges, 93 in 4.)
 int gate_up_splits(const TiledShape& t, int T) {
   const int N = 2 * t.ffn, K = t.hidden;
   if (N % 256 != 0) return 0;
@@ -204,7 +208,7 @@ int gate_up_splits(const TiledShape& t, int T) {
   for (int sp = 2; sp <= kMaxMidSplits; sp *= 2) {
     if (tiles * sp > t.cus || K % (64 * sp) != 0 || (size_t)sp * T * N > t.gate_up_room) break;
     const double range = (double)K / sp, plane = 1e-6 * sp * T * N;
-    const double c = T <= 192 ? 10 + range / 66 + 1.5 * plane : 10 + range / 58 + 1.2 * plane;
+    const double c = T <= 192 ? 12 + range / 76 + 0.7 * plane : 10 + range / 58 + 1.2 * plane;
     if (c < cost) best = sp, cost = c;
   }
   return best;

@@ -162,6 +162,7 @@ void gate_up_check() {
   struct { int T, N, K, sp; } split[] = {
       {150, 7168, 8192, 8}, {600, 7168, 8192, 2}, {400, 14336, 8192, 2}, {150, 14336, 8192, 4},
       {200, 3584, 4096, 8}, {513, 512, 2048, 8},
+      {130, 7168, 2048, 8}, {160, 11264, 2560, 4}, {130, 14336, 2560, 4}, {160, 24576, 2048, 2},
   };
   for (auto c : split) {
     const int sp = splits(c.T, c.N / 2, c.K);
